@@ -354,10 +354,10 @@ void vsr_destroy(vsr_ctx *ctx);
  * bracketed by HIP events on the context's stream. Stage s of the prefix pass
  * is s, of the candidate pass (score, reliability) VSR_STAGE_KINDS + s, of the
  * draft pass 2 VSR_STAGE_KINDS + s (there kind 9 is the LM head + chunk argmax
- * and kind 11 the greedy pick), of the fused pass of vsr_verify on bf16
- * contexts 3 VSR_STAGE_KINDS + s (there kind 3 is the prefix rows' attention,
- * kind 15 the candidate rows'; on fp32 contexts vsr_verify records prefix and
- * candidate passes);
+ * and kind 11 the greedy pick), of the fused pass of vsr_verify
+ * 3 VSR_STAGE_KINDS + s (there kind 3 is the prefix rows' attention, kind 15
+ * the candidate rows'; fp32 contexts do both in kind 3 and apply the norms in
+ * kinds 2, 6 and 9);
  * kinds: 0 embedding, 1 RMSNorm, 2 QKV projection + rotary + cache write,
  * 3 attention, 4 attention merge, 5 output projection, 6 gate/up + SwiGLU,
  * 7 down projection, 8 LM-head inputs, 9 LM head + chunk LSE,

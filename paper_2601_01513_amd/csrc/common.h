@@ -389,36 +389,36 @@ hipError_t attn_prefill(const AttnArgs &a, bool precise, hipStream_t s);
 hipError_t attn_cascade(const AttnArgs &a, bool precise, hipStream_t s);
 hipError_t attn_merge(const AttnArgs &a, hipStream_t s);
 
-// ------------------------------------------------------ simple (fp32) path
-// Plain kernels, one output element per thread; the path of VSR_F32 contexts.
-template <typename T>
-hipError_t simple_qkv_rope(const T *A, const T *W, int rows, int K, int n_heads, int n_kv,
-                           int hd, const QKVOut<T> &out, hipStream_t s);
-template <typename T>
-hipError_t simple_residual(const T *A, const T *W, int rows, int N, int K, float *x,
-                           hipStream_t s);
-template <typename T>
-hipError_t simple_swiglu(const T *A, const T *W, int rows, int F, int K, T *h, hipStream_t s);
-template <typename T>
-hipError_t simple_lmhead(const T *A, const T *W, int rows, int vocab, int K,
-                         const int32_t *lm_tgt, float2 *part, float *tgt_logit,
-                         hipStream_t s);
-// Attention with the same key rules as AttnArgs (mode 0: causal over the
-// prefix cache; mode 1: prefix + own candidate), one block per (token, head).
-struct SimpleAttnArgs {
-  const void *q, *k, *vt, *bk, *bvt;
-  int kv_npos, bk_npos;
-  const int32_t *row_lo;
-  const int32_t *q_pos;  // mode 1: branch-cache position of each query (NULL: token)
-  int T, t0, P, n_heads, n_kv, hd;  // query tokens t0 .. T-1
-  int mode;
-  void *out;
+// ------------------------------------------------------------- fp32 contexts
+// fp32 operands and accumulation (kernels_f32.hip). The QKV and gate/up
+// projections take the residual rows and apply the RMSNorm with gain g.
+hipError_t f32_qkv_rope(const float *x, const float *g, float eps, const float *W, int rows,
+                        int K, int n_heads, int n_kv, int hd, const QKVOut<float> &out,
+                        hipStream_t s);
+hipError_t f32_residual(const float *A, const float *W, int rows, int N, int K, float *x,
+                        hipStream_t s);
+hipError_t f32_swiglu(const float *x, const float *g, float eps, const float *W, int rows, int F,
+                      int K, float *h, hipStream_t s);
+// LM head as gemm_lmhead, in chunks of 64 vocabulary entries. g not NULL: the
+// rows are RMSNorm'ed with gain g; row_lo not NULL: row t is h_last if
+// row_lo[t] == t, else A[t - 1].
+int f32_lm_chunks(int vocab);
+hipError_t f32_lmhead(const float *A, const float *g, float eps, const int32_t *row_lo,
+                      const float *h_last, const float *W, int rows, int vocab, int K,
+                      const int32_t *lm_tgt, float2 *part, float *tgt_logit, hipStream_t s);
+// Greedy LM head: as gemm_lmargmax, in chunks of 64 entries.
+hipError_t f32_lmargmax(const float *A, const float *W, int rows, int vocab, int K, float2 *part,
+                        hipStream_t s);
+// Attention of query tokens t0 .. T-1: tokens below `split` are prefix rows
+// (causal over k / vt), the others (branch row b = t - split) see prefix keys
+// 0 .. P-1 and branch keys row_lo[b] .. q_pos[b] (q_pos NULL: b).
+struct F32AttnArgs {
+  const float *q, *k, *vt, *bk, *bvt;  // Vt caches in natural position order
+  int kv_npos, bk_npos;                // multiples of 64
+  const int32_t *row_lo, *q_pos;
+  int T, t0, split, P, n_heads, n_kv, hd;
+  float *out;
 };
-template <typename T>
-hipError_t simple_attn(const SimpleAttnArgs &a, hipStream_t s);
-// Greedy LM head of the plain path: part[t] = (largest logit, index bits).
-template <typename T>
-hipError_t simple_lmargmax(const T *A, const T *W, int rows, int vocab, int K, float2 *part,
-                           hipStream_t s);
+hipError_t f32_attn(const F32AttnArgs &a, hipStream_t s);
 
 }  // namespace vsr

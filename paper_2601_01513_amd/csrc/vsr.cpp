@@ -93,13 +93,12 @@ Plan make_plan(const vsr_config &c) {
   p.max_t = c.max_cands * c.max_cand_len;
   p.bk_npos = (int)align_up(p.max_t, 64);
   p.lm_rows = std::max(p.max_t, 2 * c.max_cands);
-  // MFMA contexts run the prefix and the candidate rows of vsr_verify as one
-  // set of rows.
-  p.rows_max = std::max(c.max_prefix + (c.dtype == VSR_BF16 ? p.max_t : 0), p.lm_rows);
+  // vsr_verify runs the prefix and the candidate rows as one set of rows.
+  p.rows_max = std::max(c.max_prefix + p.max_t, p.lm_rows);
   p.dec_S = c.max_new > 0 ? c.max_cand_len + c.max_new : 0;
   p.dec_npos = c.max_new > 0 ? (int)align_up((size_t)c.max_cands * p.dec_S, 64) : 0;
   p.rope_npos = p.kv_npos + c.max_cand_len + c.max_new;
-  p.lm_chunks = c.dtype == VSR_BF16 ? lmhead_chunks(c.vocab) : 1;
+  p.lm_chunks = c.dtype == VSR_BF16 ? lmhead_chunks(c.vocab) : f32_lm_chunks(c.vocab);
   // Largest partial-row count of the cascade split over every T <= max_t
   // (the split grows with the keys a block walks, at most the whole prefix
   // plus the largest branch span: a candidate, or every draft branch).
@@ -377,7 +376,7 @@ namespace {
 // One decoder block over `rows` rows whose residual stream is x. `mode` 0 is
 // the prefix (causal, caches of layer l), 1 the candidates (cascade).
 // TW is the weight type, TA the activation type (bf16 / fp16 on the MFMA
-// path, float / float on the plain path).
+// path, float / float in fp32 contexts).
 template <typename TW, typename TA>
 int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
   constexpr bool kMfma = std::is_same<TA, f16>::value;
@@ -393,9 +392,9 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
   // mode 2 (draft): branch keys/values go to the persistent draft cache at
   // the rows' cache positions; queries see the prefix and their branch up to
   // their own position.
-  // mode 3 (fused verify pass, MFMA path): rows 0 .. P-1 are the prefix (mode
-  // 0 for them), rows P .. rows-1 the candidates (mode 1): one set of rows
-  // through every projection, two attention launches per layer.
+  // mode 3 (fused verify pass): rows 0 .. P-1 are the prefix (mode 0 for
+  // them), rows P .. rows-1 the candidates (mode 1): one set of rows through
+  // every projection; two attention launches per layer on the MFMA path.
   const bool draft = mode == 2;
   const bool fused = mode == 3;
   const int P = c->P;
@@ -419,11 +418,13 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
     // The feed-forward block of a precise layer is split too only in the
     // first split_mlp_layers layers.
     const int spm = kMfma && l < cf.split_mlp_layers ? 2 : 1;
-    if (!xn_ready)
-      STAGE(c, K_NORM, "attention norm",
-            launch_rmsnorm<TW, TA>(x, static_cast<const TW *>(c->attn_norm[l]), rows, d,
-                                   cf.rms_eps, xn, sp, s));
-    xn_ready = false;
+    const TW *attn_g = static_cast<const TW *>(c->attn_norm[l]);
+    if constexpr (kMfma) {  // (the fp32 projections apply the norms themselves)
+      if (!xn_ready)
+        STAGE(c, K_NORM, "attention norm",
+              launch_rmsnorm<TW, TA>(x, attn_g, rows, d, cf.rms_eps, xn, sp, s));
+      xn_ready = false;
+    }
     QKVOut<TA> qo;
     qo.q = q;
     // The fast attention kernels take the queries pre-scaled (log2 units).
@@ -476,7 +477,7 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
               gemm_qkv_rope(xn, wqkv, wf16, rows, d, sp, Hq, Hkv, qo, gpart, s));
     } else {
       STAGE(c, K_QKV, "qkv projection",
-            simple_qkv_rope<TA>(xn, wqkv, rows, d, Hq, Hkv, hd, qo, s));
+            f32_qkv_rope(x, attn_g, cf.rms_eps, wqkv, rows, d, Hq, Hkv, hd, qo, s));
     }
     // The prefix's last layer only feeds the last prefix row (the hidden state
     // that predicts candidate token 0): its keys/values are needed for every
@@ -541,7 +542,7 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
         STAGE(c, K_MERGE, "cascade merge", attn_merge(a, s));
       }
     } else {
-      SimpleAttnArgs a{};
+      F32AttnArgs a{};
       a.q = q;
       a.k = kc;
       a.vt = vtc;
@@ -552,14 +553,14 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
       a.row_lo = c->at<int32_t>(p.row_lo);
       a.q_pos = cache_row;
       a.T = rows;
+      a.t0 = r0;
+      a.split = mode == 0 ? rows : fused ? P : 0;
       a.P = c->P;
       a.n_heads = Hq;
       a.n_kv = Hkv;
       a.hd = hd;
-      a.t0 = r0;
-      a.mode = mode == 0 ? 0 : 1;
       a.out = attn;
-      STAGE(c, K_ATTN, "attention", simple_attn<TA>(a, s));
+      STAGE(c, K_ATTN, "attention", f32_attn(a, s));
     }
     const TA *attn_r = attn + (size_t)r0 * Hq * hd * sp;
     float *x_r = x + (size_t)r0 * d;
@@ -587,18 +588,19 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
             gemm_residual(attn_r, wo, wf16, nr, d, Hq * hd, sp, x_r, gpart, s));
     } else {
       STAGE(c, K_OPROJ, "output projection",
-            simple_residual<TA>(attn_r, wo, nr, d, Hq * hd, x_r, s));
+            f32_residual(attn_r, wo, nr, d, Hq * hd, x_r, s));
     }
-    STAGE(c, K_NORM, "ffn norm",
-          launch_rmsnorm<TW, TA>(x_r, ffn_g, nr, d, cf.rms_eps, xn, spm, s));
     if constexpr (kMfma) {
+      STAGE(c, K_NORM, "ffn norm",
+            launch_rmsnorm<TW, TA>(x_r, ffn_g, nr, d, cf.rms_eps, xn, spm, s));
       STAGE(c, K_GATEUP, "gate/up projection",
             gemm_swiglu(xn, wgu, wf16, nr, F, d, spm, h, gpart, s));
       STAGE(c, K_DOWN, "down projection",
             gemm_residual(h, wdown, wf16, nr, d, F, spm, x_r, gpart, s));
     } else {
-      STAGE(c, K_GATEUP, "gate/up projection", simple_swiglu<TA>(xn, wgu, nr, F, d, h, s));
-      STAGE(c, K_DOWN, "down projection", simple_residual<TA>(h, wdown, nr, d, F, x_r, s));
+      STAGE(c, K_GATEUP, "gate/up projection",
+            f32_swiglu(x_r, ffn_g, cf.rms_eps, wgu, nr, F, d, h, s));
+      STAGE(c, K_DOWN, "down projection", f32_residual(h, wdown, nr, d, F, x_r, s));
     }
   }
   return VSR_OK;
@@ -658,38 +660,46 @@ int lm_head(vsr_ctx *c, int rows, int *chunks) {
   int32_t *lm_tgt = c->at<int32_t>(p.lm_tgt);
   float2 *lm_part = c->at<float2>(p.lm_part);
   float *tgt = c->at<float>(p.tgt);
-  if constexpr (kMfma) {
-    *chunks = lmhead_chunks(cf.vocab);
+  *chunks = p.lm_chunks;
+  if constexpr (kMfma)
     STAGE(c, K_LMHEAD, "lm head",
           gemm_lmhead(lm_in, c->lm_head, cf.gemm_weights == VSR_F16, rows, cf.vocab,
                       cf.d_model, lm_tgt, lm_part, tgt, s));
-  } else {
-    *chunks = 1;
+  else
     STAGE(c, K_LMHEAD, "lm head",
-          simple_lmhead<TA>(lm_in, static_cast<const TW *>(c->lm_head), rows, cf.vocab,
-                            cf.d_model, lm_tgt, lm_part, tgt, s));
-  }
+          f32_lmhead(lm_in, nullptr, 0.f, nullptr, nullptr, static_cast<const TW *>(c->lm_head),
+                     rows, cf.vocab, cf.d_model, lm_tgt, lm_part, tgt, s));
   return VSR_OK;
 }
 
+// Candidate rows (residual stream xc) to log-probs, scores and the argmax:
+// final norm of each row's predecessor, LM head, LSE, sums, selection.
 template <typename TW, typename TA>
-int score_impl(vsr_ctx *c, const Branches &br, const int32_t *cand_ids, float *logprobs,
-               float *scores, int32_t *argmax) {
+int score_tail(vsr_ctx *c, const Branches &br, const float *xc, float *logprobs, float *scores,
+               int32_t *argmax) {
+  constexpr bool kMfma = std::is_same<TA, f16>::value;
   const vsr_config &cf = c->cfg;
   const Plan &p = c->plan;
-  const int T_rows = br.cu[br.M];
   hipStream_t s = c->stream;
+  const int T_rows = br.cu[br.M];
+  const TW *g = static_cast<const TW *>(c->final_norm);
+  const float *h_last = c->at<float>(p.h_last);
+  const int32_t *row_lo = c->at<int32_t>(p.row_lo);
   int lm_chunks = 1;
   if (T_rows > 0) {
-    int rc = branch_forward<TW, TA>(c, br, cand_ids);
-    if (rc) return rc;
-    STAGE(c, K_LMIN, "lm inputs",
-          launch_lm_inputs<TW, TA>(c->at<float>(p.x), c->at<float>(p.h_last),
-                                   c->at<int32_t>(p.row_lo),
-                                   static_cast<const TW *>(c->final_norm), T_rows, cf.d_model,
-                                   cf.rms_eps, c->at<TA>(p.xn), s));
-    rc = lm_head<TW, TA>(c, T_rows, &lm_chunks);
-    if (rc) return rc;
+    if constexpr (kMfma) {
+      STAGE(c, K_LMIN, "lm inputs",
+            launch_lm_inputs<TW, TA>(xc, h_last, row_lo, g, T_rows, cf.d_model, cf.rms_eps,
+                                     c->at<TA>(p.xn), s));
+      const int rc = lm_head<TW, TA>(c, T_rows, &lm_chunks);
+      if (rc) return rc;
+    } else {
+      lm_chunks = p.lm_chunks;
+      STAGE(c, K_LMHEAD, "lm head",
+            f32_lmhead(xc, g, cf.rms_eps, row_lo, h_last, static_cast<const TW *>(c->lm_head),
+                       T_rows, cf.vocab, cf.d_model, c->at<int32_t>(p.lm_tgt),
+                       c->at<float2>(p.lm_part), c->at<float>(p.tgt), s));
+    }
   }
   STAGE(c, K_LSE, "lse gather",
         launch_lse_gather(br, c->at<float2>(p.lm_part), lm_chunks, c->at<float>(p.tgt),
@@ -698,7 +708,17 @@ int score_impl(vsr_ctx *c, const Branches &br, const int32_t *cand_ids, float *l
   return VSR_OK;
 }
 
-// Prefix and candidates in one pass (MFMA contexts): the prefix rows and the
+template <typename TW, typename TA>
+int score_impl(vsr_ctx *c, const Branches &br, const int32_t *cand_ids, float *logprobs,
+               float *scores, int32_t *argmax) {
+  if (br.cu[br.M] > 0) {
+    const int rc = branch_forward<TW, TA>(c, br, cand_ids);
+    if (rc) return rc;
+  }
+  return score_tail<TW, TA>(c, br, c->at<float>(c->plan.x), logprobs, scores, argmax);
+}
+
+// Prefix and candidates in one pass: the prefix rows and the
 // candidate rows go through every projection together (one GEMM launch per
 // projection for both); per layer, the prefix rows attend causally over the
 // prefix cache and the candidate rows over the prefix + their own keys. The
@@ -726,25 +746,16 @@ int verify_impl(vsr_ctx *c, const void *visual, int nv, const int32_t *ids, int 
   STAGE(c, K_EMBED, "candidate embedding",
         launch_embed_rows<TW>(lm_tgt, T_rows, static_cast<const TW *>(c->embed), cf.d_model, xc,
                               s));
-  const Split split = cascade_split(T_rows, P + br.cmax, cf.n_heads, cf.n_kv_heads);
-  int rc = run_layers<TW, TA>(c, P + T_rows, 3, split);
+  constexpr bool kMfma = std::is_same<TA, f16>::value;
+  const Split split =
+      kMfma ? cascade_split(T_rows, P + br.cmax, cf.n_heads, cf.n_kv_heads) : Split{1};
+  const int rc = run_layers<TW, TA>(c, P + T_rows, 3, split);
   if (rc) return rc;
   STAGE(c, K_COPY, "last prefix row",
         hipMemcpyAsync(c->at<float>(p.h_last), x + (size_t)(P - 1) * cf.d_model,
                        (size_t)cf.d_model * 4, hipMemcpyDeviceToDevice, s));
   c->prefilled = true;
-  STAGE(c, K_LMIN, "lm inputs",
-        launch_lm_inputs<TW, TA>(xc, c->at<float>(p.h_last), row_lo,
-                                 static_cast<const TW *>(c->final_norm), T_rows, cf.d_model,
-                                 cf.rms_eps, c->at<TA>(p.xn), s));
-  int lm_chunks = 1;
-  rc = lm_head<TW, TA>(c, T_rows, &lm_chunks);
-  if (rc) return rc;
-  STAGE(c, K_LSE, "lse gather",
-        launch_lse_gather(br, c->at<float2>(p.lm_part), lm_chunks, c->at<float>(p.tgt),
-                          logprobs, s));
-  STAGE(c, K_SELECT, "reduce/select", launch_reduce_select(br, logprobs, scores, argmax, s));
-  return VSR_OK;
+  return score_tail<TW, TA>(c, br, xc, logprobs, scores, argmax);
 }
 
 template <typename TW, typename TA>
@@ -788,7 +799,7 @@ int draft_impl(vsr_ctx *c, const Branches &br, const int32_t *ids, int n_new, in
   const TW *g = static_cast<const TW *>(c->final_norm);
   const bool wf16 = cf.gemm_weights == VSR_F16;
   const bool skinny_lm = kMfma && M <= kSkinnyMaxRows && skinny_lm_chunks(cf.vocab) > 0;
-  const int chunks = !kMfma ? 1 : skinny_lm ? skinny_lm_chunks(cf.vocab) : lmhead_chunks(cf.vocab);
+  const int chunks = skinny_lm ? skinny_lm_chunks(cf.vocab) : p.lm_chunks;
   auto pick = [&](int step) -> int {
     if constexpr (kMfma) {
       if (skinny_lm)
@@ -799,8 +810,8 @@ int draft_impl(vsr_ctx *c, const Branches &br, const int32_t *ids, int n_new, in
               gemm_lmargmax(lm_in, c->lm_head, wf16, M, cf.vocab, cf.d_model, part, s));
     } else {
       STAGE(c, K_LMHEAD, "draft lm head",
-            simple_lmargmax<TA>(lm_in, static_cast<const TW *>(c->lm_head), M, cf.vocab,
-                                cf.d_model, part, s));
+            f32_lmargmax(lm_in, static_cast<const TW *>(c->lm_head), M, cf.vocab, cf.d_model,
+                         part, s));
     }
     STAGE(c, K_SELECT, "draft pick",
           launch_argmax_merge(part, chunks, M, n_new, step, tokens, next_ids, s));
@@ -968,13 +979,16 @@ extern "C" int vsr_verify(vsr_ctx *ctx, const void *visual, int32_t n_visual,
   ctx->prefilled = false;
   rc = checks_begin(ctx);
   if (rc) return rc;
-  if (ctx->cfg.dtype == VSR_BF16 && br.cu[M] > 0) {
+  if (br.cu[M] > 0) {
     ctx->phase = 3;
-    rc = verify_impl<bf16, f16>(ctx, visual, n_visual, ids, n_text, br, cand_ids, logprobs,
-                                scores, argmax);
+    rc = ctx->cfg.dtype == VSR_BF16
+             ? verify_impl<bf16, f16>(ctx, visual, n_visual, ids, n_text, br, cand_ids, logprobs,
+                                      scores, argmax)
+             : verify_impl<float, float>(ctx, visual, n_visual, ids, n_text, br, cand_ids,
+                                         logprobs, scores, argmax);
     return checks_end(ctx, rc, scores, M);
   }
-  // fp32 contexts, or no candidate tokens: the two passes one after the other.
+  // No candidate tokens: the two passes one after the other.
   ctx->phase = 0;
   rc = ctx->cfg.dtype == VSR_BF16
            ? prefill_impl<bf16, f16>(ctx, visual, n_visual, ids, n_text)

@@ -1,0 +1,95 @@
+"""fp32 contexts against the oracle where their kernels can go wrong: widths
+that are no multiple of the 16-wide pieces (loads by element), odd head
+dimensions, one-row calls, both tile sizes of the projections, partial last
+tiles everywhere, and non-finite rows that other candidates must not see.
+
+Tolerance: 1e-4 per token, the bar of the fp32 path (float32 sums of at most
+2112 terms of unit-scale products against float64: measured below 3e-6)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_01513_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _cfg(d, hq, hkv, hd, ff, vocab, p, pv, m, c):
+    return W.VerifierConfig(
+        name=f"fp32 d{d} {hq}/{hkv}x{hd} F{ff} V{vocab} P{p} M{m}x{c}", n_layers=2, d_model=d,
+        n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=ff, vocab=vocab, rope_base=10000.0,
+        dtype=W.F32, n_prefix=p, n_visual=pv, n_cands=m, cand_len=c)
+
+
+CASES = [
+    _cfg(100, 3, 3, 36, 70, 333, 1, 0, 1, 1),          # by element; one prefix row
+    _cfg(72, 2, 1, 6, 50, 65, 18, 18, 3, 5),           # head dim not a multiple of 4
+    _cfg(256, 4, 2, 64, 704, 1000, 33, 7, 3, 17),      # one row past a tile
+    _cfg(96, 4, 1, 128, 112, 257, 65, 1, 2, 33),       # 8 pieces of the head dim
+    _cfg(128, 2, 2, 200, 144, 500, 100, 50, 4, 20),    # 13 of 16 pieces
+    _cfg(64, 4, 4, 16, 2112, 33000, 500, 100, 5, 14),  # 32-row tiles (FFN, LM head)
+]
+
+
+def _inputs(cfg, seed):
+    torch = _torch()
+    wl = W.make_workload(cfg, seed, device="cuda")
+    lens = np.asarray([cfg.cand_len - (m * cfg.cand_len) // (cfg.n_cands + 1)
+                       for m in range(cfg.n_cands)], dtype=np.int32)
+    for m in range(cfg.n_cands):
+        wl.cand_ids[m, lens[m]:] = 0
+    wl.cand_len = lens
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda") if cfg.n_text else None
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    return wl, wl.visual if cfg.n_visual else None, ids, cids
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_f32_passes(cfg):
+    torch = _torch()
+    from paper_2601_01513_amd.binding import Verifier
+    wl, vis, ids, cids = _inputs(cfg, 1)
+    v = Verifier(cfg, wl.weights, device="cuda", max_new=2)
+    ref, _, am = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights),
+                                            W.to_host_f32(wl.visual), wl.prefix_ids, wl.cand_ids,
+                                            wl.cand_len)
+    one = v.verify(vis, ids, cids, wl.cand_len)
+    v.prefill(vis, ids)
+    two = v.score(cids, wl.cand_len)
+    # The first greedy token of a branch is the argmax of its last row; its
+    # log-prob, scored as one more token, is the largest of that row.
+    tok = v.draft(cids, wl.cand_len, 2)
+    torch.cuda.synchronize()
+    for out in (one, two):
+        assert np.abs(out[0].cpu().numpy() - ref).max() <= 1e-4
+        assert int(out[2].cpu()[0]) == am
+    assert tok.min() >= 0 and tok.max() < cfg.vocab
+
+
+def test_f32_candidates_do_not_see_each_others_nan():
+    """Candidate 1 reads an embedding row of NaN; candidates 0 and 2, in the
+    same row and key tiles, keep their log-probs, and candidate 1 keeps those
+    of its earlier tokens."""
+    torch = _torch()
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = _cfg(64, 2, 2, 32, 96, 200, 20, 4, 3, 6)
+    wl, vis, ids, cids = _inputs(cfg, 2)
+    wl.weights["embed"][7] = float("nan")
+    cids[cids == 7] = 8
+    if ids is not None:
+        ids[ids == 7] = 8
+    v = Verifier(cfg, wl.weights, device="cuda")
+    lens = [6, 6, 6]
+    clean = v.verify(vis, ids, cids, lens)[0].cpu().numpy()
+    cids[1, 3] = 7
+    got = v.verify(vis, ids, cids, lens)[0].cpu().numpy()
+    np.testing.assert_array_equal(got[[0, 2]], clean[[0, 2]])
+    np.testing.assert_array_equal(got[1, :3], clean[1, :3])
+    assert np.isnan(got[1, 4:]).all()
