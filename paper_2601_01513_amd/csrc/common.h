@@ -36,20 +36,49 @@ template <> __device__ __forceinline__ f16 from_f32<f16>(float x) { return stati
 // Largest number of candidates one score call may carry.
 constexpr int kMaxCands = 256;
 
-// Packed candidate rows: candidate m owns rows [cu[m], cu[m+1]).
-// Sum / maximum over the 64 lanes of a wave (butterfly, fixed order), the
-// result in every lane.
+// Sum / maximum over the 64 lanes of a wave (fixed order), the result in every
+// lane. Row shifts and broadcasts within the vector ALU; a butterfly of
+// __shfl_xor is six dependent LDS permutes, about 0.2 us, which showed in every
+// small latency-bound kernel.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_f32(float old, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL,
+                                                    ROWS, 0xF, false));
+}
+__device__ __forceinline__ float lane63(float v) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_f32<0x111, 0xF>(0.f, v);  // row_shr 1, 2, 4, 8: lane 15 of each row has its sum
+  v += dpp_f32<0x112, 0xF>(0.f, v);
+  v += dpp_f32<0x114, 0xF>(0.f, v);
+  v += dpp_f32<0x118, 0xF>(0.f, v);
+  v += dpp_f32<0x142, 0xA>(0.f, v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_f32<0x143, 0xC>(0.f, v);  // row_bcast 31 into rows 2 and 3
+  return lane63(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  v = fmaxf(v, dpp_f32<0x111, 0xF>(v, v));  // lanes without a source keep their own
+  v = fmaxf(v, dpp_f32<0x112, 0xF>(v, v));
+  v = fmaxf(v, dpp_f32<0x114, 0xF>(v, v));
+  v = fmaxf(v, dpp_f32<0x118, 0xF>(v, v));
+  v = fmaxf(v, dpp_f32<0x142, 0xA>(v, v));
+  v = fmaxf(v, dpp_f32<0x143, 0xC>(v, v));
+  return lane63(v);
+}
+
+// Inclusive prefix sum over the lanes of a wave.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
   return v;
 }
 
+// Packed candidate rows: candidate m owns rows [cu[m], cu[m+1]).
 struct Branches {
   int M;
   int cmax;

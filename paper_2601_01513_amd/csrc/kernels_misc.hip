@@ -411,80 +411,277 @@ hipError_t launch_reliability_finish(int M, const float2 *part, int nchunks,
 }
 
 // --------------------------------------------- entity alignment and choice
-// Block m (16 waves): wave w takes frames w, w+16, ...; lanes stride over the
-// D coordinates. cos = (e . f) / (|e| |f|), 0 if either norm is 0.
+// cos = (e . f) / (|e| |f|), 0 if either norm is 0.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Few frames: block m (16 waves) takes draft m against every frame, a wave
+// four frames at a time, the lanes four coordinates each. Latency-bound: the
+// loads of the four frames are in flight together and the sums stay in
+// registers (one frame after the other, with LDS permutes for the sums, took
+// 11 us for 8 x 64 x 768; now 5.2 us).
 __global__ __launch_bounds__(1024) void k_align(const float *ent, const float *frames, int NF,
                                                 int D, float *align) {
   __shared__ float red[16];
   const int m = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float *e = ent + (long)m * D;
-  float ee = 0.f;
-  for (int c = lane; c < D; c += 64) ee += e[c] * e[c];
-  ee = wave_sum(ee);
+  auto ld = [&](const float *p, int c) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (c + 3 < D)
+      v = *reinterpret_cast<const f32x4u *>(p + c);
+    else
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (c + j < D) v[j] = p[c + j];
+    return v;
+  };
   float best = -INFINITY;
-  for (int f = w; f < NF; f += 16) {
-    const float *fr = frames + (long)f * D;
-    float ef = 0.f, ff = 0.f;
-    for (int c = lane; c < D; c += 64) {
-      const float v = fr[c];
-      ef += e[c] * v;
-      ff += v * v;
+  for (int f = w; f < NF; f += 64) {
+    float ee = 0.f, ef[4] = {0.f, 0.f, 0.f, 0.f}, ff[4] = {0.f, 0.f, 0.f, 0.f};
+    const float *fr[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fr[j] = frames + (long)min(f + 16 * j, NF - 1) * D;
+    for (int c0 = 4 * lane; c0 < D; c0 += 768) {
+      f32x4 x[3], y[3][4];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        x[i] = ld(e, c0 + 256 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[i][j] = ld(fr[j], c0 + 256 * i);
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          ee += x[i][k] * x[i][k];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            ef[j] += x[i][k] * y[i][j][k];
+            ff[j] += y[i][j][k] * y[i][j][k];
+          }
+        }
     }
-    ef = wave_sum(ef);
-    ff = wave_sum(ff);
-    const float den = sqrtf(ee) * sqrtf(ff);
-    best = fmaxf(best, den > 0.f ? ef / den : 0.f);
+    ee = wave_sum(ee);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float den = sqrtf(ee) * sqrtf(wave_sum(ff[j]));
+      const float dot = wave_sum(ef[j]);
+      best = fmaxf(best, den > 0.f ? dot / den : 0.f);  // (a repeated last frame: no change)
+    }
   }
   if (lane == 0) red[w] = best;
   __syncthreads();
   if (threadIdx.x == 0) {
     float b = red[0];
+#pragma unroll
     for (int i = 1; i < 16; ++i) b = fmaxf(b, red[i]);
     align[m] = b;
   }
 }
 
-// First index of the largest value among the allowed ones (-1 if none).
-__device__ __forceinline__ int argmax_where(const float *v, const bool *ok, int n) {
-  int best = -1;
-  for (int i = 0; i < n; ++i)
-    if (ok[i] && (best < 0 || v[i] > v[best])) best = i;
-  return best;
+// Many frames: a block of 16 waves takes 16 drafts x 64 frames at a time as
+// fp32 matrix products: wave w has frames 16 (w % 4) .. + 15 of the 64 and
+// every fourth 16-wide piece of D; the partial products and the rows' squares
+// meet in LDS. 64 drafts x 2048 frames x 1024: 645 us with a block per draft and
+// a frame at a time, now 23 us.
+constexpr int AL_M = 16, AL_F = 64, AL_T = 1024;
+
+struct AlignTile {
+  float red[16][256];
+  float ee[4][16], ff[4][4][16];
+};
+
+// The largest cosine of drafts m0 .. m0 + 15 over frames f0, f0 + AL_F, ...
+// (step frames apart, below NF): thread t < 64 gets draft m0 + t / 4's maximum
+// over the 16-frame groups t % 4 of its tiles.
+__device__ __forceinline__ float align_tiles(AlignTile &s, const float *ent, const float *frames,
+                                             int M, long NF, int D, int m0, long f0, long step) {
+  __shared__ float best[AL_M][4];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63, c16 = lane & 15, sub = 4 * (lane >> 4);
+  const int fg = w & 3, kq = w >> 2, np = (D + 15) / 16, nfull = D / 16;
+  const float *ep = ent + (long)min(m0 + c16, M - 1) * D + sub;
+  if (t < AL_M * 4) best[t >> 2][t & 3] = -INFINITY;
+  constexpr int U = 4;  // pieces in flight
+  for (long f = f0; f < NF; f += step) {
+    const float *fp = frames + min(f + 16 * fg + c16, NF - 1) * D + sub;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float ee = 0.f, ff = 0.f;
+    auto add = [&](f32x4 e, f32x4 x) {
+      ee += e[0] * e[0] + e[1] * e[1] + e[2] * e[2] + e[3] * e[3];
+      ff += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(e[j], x[j], acc, 0, 0, 0);
+    };
+    for (int p = kq; p < nfull; p += 4 * U) {
+      f32x4 e[U], x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = 16 * min(p + 4 * u, nfull - 1);
+        e[u] = *reinterpret_cast<const f32x4u *>(ep + k);
+        x[u] = *reinterpret_cast<const f32x4u *>(fp + k);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p + 4 * u < nfull) add(e[u], x[u]);
+    }
+    if (np > nfull && nfull % 4 == kq) {  // the last, partial piece
+      f32x4 e, x;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = 16 * nfull + sub + j < D;
+        e[j] = in ? ep[16 * nfull + j] : 0.f;
+        x[j] = in ? fp[16 * nfull + j] : 0.f;
+      }
+      add(e, x);
+    }
+    ee += __shfl_xor(ee, 16, 64);
+    ee += __shfl_xor(ee, 32, 64);
+    ff += __shfl_xor(ff, 16, 64);
+    ff += __shfl_xor(ff, 32, 64);
+    __syncthreads();  // the previous tile's values are used
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s.red[w][64 * r + lane] = acc[r];
+    if (lane < 16) {
+      s.ff[fg][kq][lane] = ff;
+      if (fg == 0) s.ee[kq][lane] = ee;
+    }
+    __syncthreads();
+    // Thread t: 16-frame group t / 256, draft row 4 ((t % 64) / 16) +
+    // (t % 256) / 64, frame column t % 16.
+    const int g = t >> 8, el = t & 255, row = 4 * ((el & 63) >> 4) + (el >> 6);
+    const float dot = (s.red[g][el] + s.red[g + 4][el]) + (s.red[g + 8][el] + s.red[g + 12][el]);
+    const float se = (s.ee[0][row] + s.ee[1][row]) + (s.ee[2][row] + s.ee[3][row]);
+    const float sf = (s.ff[g][0][c16] + s.ff[g][1][c16]) + (s.ff[g][2][c16] + s.ff[g][3][c16]);
+    const float den = sqrtf(se) * sqrtf(sf);
+    float v = f + 16 * g + c16 < NF ? (den > 0.f ? dot / den : 0.f) : -INFINITY;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    if (c16 == 0) best[row][g] = fmaxf(best[row][g], v);
+  }
+  __syncthreads();
+  return t < AL_M * 4 ? best[t >> 2][t & 3] : -INFINITY;
+}
+
+// The final choice by wave 0 from the alignments in LDS. An argmax takes the
+// first allowed index if its value is NaN (nothing compares greater), else
+// the lowest index of the largest value.
+__device__ __forceinline__ void choose(const float *rel, const float *al, int M, float delta,
+                                       int strategy, int32_t *choice) {
+  constexpr int E = kMaxCands / 64;
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  float filt[E], rank[E];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int m = lane + 64 * e;
+    const float r = m < M ? rel[m] : -INFINITY, a = m < M ? al[m] : -INFINITY;
+    filt[e] = strategy == 0 ? r : a;
+    rank[e] = strategy == 1 ? r + a : strategy == 0 ? a : r;
+    mx = fmaxf(mx, filt[e]);
+  }
+  mx = wave_max(mx);
+  int first = 0x7fffffff, bi = 0x7fffffff;
+  float first_v = 0.f, bv = -INFINITY;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int m = lane + 64 * e;
+    const bool ok = m < M && (strategy == 1 || filt[e] >= mx - delta);
+    if (ok && m < first) {
+      first = m;
+      first_v = rank[e];
+    }
+    if (ok && !isnan(rank[e]) && (bi == 0x7fffffff || rank[e] > bv)) {
+      bv = rank[e];
+      bi = m;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const int f2 = __shfl_xor(first, o, 64), i2 = __shfl_xor(bi, o, 64);
+    const float fv2 = __shfl_xor(first_v, o, 64), v2 = __shfl_xor(bv, o, 64);
+    if (f2 < first) {
+      first = f2;
+      first_v = fv2;
+    }
+    if (i2 != 0x7fffffff && (bi == 0x7fffffff || v2 > bv || (v2 == bv && i2 < bi))) {
+      bv = v2;
+      bi = i2;
+    }
+  }
+  if (lane == 0) *choice = first == 0x7fffffff ? -1 : isnan(first_v) ? first : bi;
 }
 
 __global__ __launch_bounds__(64) void k_choose(const float *rel, const float *align, int M,
                                                float delta, int strategy, int32_t *choice) {
-  __shared__ float r[kMaxCands], a[kMaxCands], sum[kMaxCands];
-  __shared__ bool ok[kMaxCands];
-  for (int m = threadIdx.x; m < M; m += 64) {
-    r[m] = rel[m];
-    a[m] = align[m];
-    sum[m] = r[m] + a[m];
+  choose(rel, align, M, delta, strategy, choice);
+}
+
+// Blocks over (frame tiles, draft tiles) take maxima
+// into align as order-preserving integers (atomics), counting themselves in
+// *choice; the last one decodes them and chooses. k_align_init sets both.
+__device__ __forceinline__ int32_t ordered_bits(float v) {
+  const int32_t i = __float_as_int(v);
+  return i >= 0 ? i : i ^ 0x7fffffff;
+}
+
+__global__ void k_align_init(int M, int32_t *align, int32_t *choice) {
+  for (int m = threadIdx.x; m < M; m += blockDim.x) align[m] = ordered_bits(-INFINITY);
+  if (threadIdx.x == 0) *choice = 0;
+}
+
+__global__ __launch_bounds__(AL_T) void k_align_many(const float *ent, const float *frames, int M,
+                                                     int NF, int D, const float *rel, float delta,
+                                                     int strategy, float *align,
+                                                     int32_t *choice) {
+  __shared__ AlignTile s;
+  __shared__ float al[kMaxCands];
+  __shared__ int32_t finished;
+  const int t = threadIdx.x, m0 = blockIdx.y * AL_M;
+  float v = align_tiles(s, ent, frames, M, NF, D, m0, (long)blockIdx.x * AL_F,
+                        (long)gridDim.x * AL_F);
+  v = fmaxf(v, __shfl_xor(v, 1, 64));
+  v = fmaxf(v, __shfl_xor(v, 2, 64));
+  int32_t *bits = reinterpret_cast<int32_t *>(align);
+  if (t < AL_M * 4) {  // wave 0
+    if ((t & 3) == 0 && m0 + (t >> 2) < M)
+      __hip_atomic_fetch_max(&bits[m0 + (t >> 2)], ordered_bits(v), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the maxima are in
+    if (t == 0)
+      finished = __hip_atomic_fetch_add(choice, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  int best;
-  if (strategy == 1) {  // addition
-    for (int m = 0; m < M; ++m) ok[m] = true;
-    best = argmax_where(sum, ok, M);
-  } else {
-    const float *filt = strategy == 0 ? r : a, *rank = strategy == 0 ? a : r;
-    float mx = filt[0];
-    for (int m = 1; m < M; ++m) mx = fmaxf(mx, filt[m]);
-    for (int m = 0; m < M; ++m) ok[m] = filt[m] >= mx - delta;
-    best = argmax_where(rank, ok, M);
+  if (finished != (int)(gridDim.x * gridDim.y) - 1) return;  // uniform per block
+  if (t < M) {
+    const int32_t i =
+        __hip_atomic_load(&bits[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const float x = __int_as_float(i >= 0 ? i : i ^ 0x7fffffff);
+    al[t] = x;
+    align[t] = x;
   }
-  *choice = best;
+  __syncthreads();
+  choose(rel, al, M, delta, strategy, choice);
 }
 
 hipError_t launch_align_select(const float *ent, const float *frames, int M, int NF, int D,
                                const float *rel, float delta, int strategy, float *align,
                                int32_t *choice, hipStream_t s) {
-  k_align<<<M, 1024, 0, s>>>(ent, frames, NF, D, align);
-  k_choose<<<1, 64, 0, s>>>(rel, align, M, delta, strategy, choice);
+  // A block per draft walks the frames at 3 to 4.5 us per 64 of them; the tiled
+  // form takes 11 to 21 us up to 2048 frames. They cross near 192 frames: 128
+  // frames of 768 10 against 17 us, 170 of 1024 18 against 19, 256 of 512 16
+  // against 13.
+  if (NF <= 192) {
+    k_align<<<M, 1024, 0, s>>>(ent, frames, NF, D, align);
+    k_choose<<<1, 64, 0, s>>>(rel, align, M, delta, strategy, choice);
+  } else {
+    k_align_init<<<1, 256, 0, s>>>(M, reinterpret_cast<int32_t *>(align), choice);
+    const dim3 grid((unsigned)std::min<long>(((long)NF + AL_F - 1) / AL_F, 2048),
+                    (M + AL_M - 1) / AL_M);
+    k_align_many<<<grid, AL_T, 0, s>>>(ent, frames, M, NF, D, rel, delta, strategy, align, choice);
+  }
   return hipGetLastError();
 }
-
 
 // One wave per output slot (m, j); lanes stride over the vocabulary chunks.
 __global__ __launch_bounds__(256) void k_lse_gather(Branches br, const float2 *part,
