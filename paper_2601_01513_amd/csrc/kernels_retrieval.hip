@@ -6,6 +6,7 @@
 // calls give identical results: histogram counts are integer LDS atomics;
 // the keyframe test compares an integer sum with theta * 3HW in float64;
 // rankings break ties by the lower document index.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -17,456 +18,511 @@ namespace {
 constexpr int BINS = 64;            // per channel, bin = value >> 2
 constexpr int HB = 3 * BINS;        // bins of one frame
 constexpr int HIST_T = 1024;        // threads of the histogram block
-constexpr int HIST_W = HIST_T / 64;
-
-constexpr int HIST_SPLIT = 4;       // blocks per frame
 
 __global__ void k_zero_i32(int32_t *p, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
 
-// Block (f, part): the histogram of part `part` of HIST_SPLIT of frame f's
-// 16-byte chunks (and, for the last part, its trailing bytes), added into
-// hist[f] (zeroed before) with integer atomics: exact, so the counts do not
-// depend on the order. Each wave counts into its own LDS copy, then the
-// copies are summed.
+// Block (f, part): the histogram of part `part` of `split` of frame f. The
+// counts are LDS atomics; the pixels of a scene fall into few bins, so with
+// one copy of the histogram per wave most lanes of an atomic met in the same
+// word and the copies' serialization bounded the kernel (37 us for 220 frames
+// of 336 x 336, 2.0 TB/s). Here every bin has 64 words, one per lane and one
+// per LDS bank: lane l counts bin b at word 64 b + l, no two lanes of an
+// instruction share a bank, and all waves of the block share the copies.
+// Now 19.7 us (3.8 TB/s; HBM and the atomics' own rate about balance).
+// ATOMIC: parts of a frame add into hist (zeroed before) with integer atomics,
+// exact in any order; otherwise the block stores the frame's counts.
+template <bool ATOMIC>
 __global__ __launch_bounds__(HIST_T) void k_hist(const uint8_t *frames, long frame_bytes,
-                                                 int32_t *hist) {
-  __shared__ int32_t h[HIST_W][HB];
-  const int t = threadIdx.x, w = t >> 6;
-  const int f = blockIdx.x / HIST_SPLIT, part = blockIdx.x % HIST_SPLIT;
-  for (int i = t; i < HIST_W * HB; i += HIST_T) (&h[0][0])[i] = 0;
-  __syncthreads();
-  const uint8_t *src = frames + (long)f * frame_bytes;
-  // 16-byte loads need every frame 16-byte aligned (the base is, by contract).
-  const long n16 = frame_bytes % 16 == 0 ? frame_bytes / 16 : 0;
-  const long i0 = n16 * part / HIST_SPLIT, i1 = n16 * (part + 1) / HIST_SPLIT;
-  // Byte b of the frame belongs to channel b % 3; a 16-byte chunk at byte
-  // 16 i starts at channel (16 i) % 3 = i % 3.
-  // Batches of HIST_B chunks per thread, all loads issued before counting.
-  constexpr int HIST_B = 8;
-  for (long i = i0 + t; i < i1; i += (long)HIST_B * HIST_T) {
-    u32x4 v[HIST_B];
+                                                 int split, int32_t *hist) {
+  __shared__ __align__(16) uint32_t h[HB * 64];
+  const int t = threadIdx.x, lane = t & 63;
+  const int f = blockIdx.x / split, part = blockIdx.x % split;
+  for (int i = t; i < HB * 16; i += HIST_T) reinterpret_cast<u32x4 *>(h)[i] = u32x4{0, 0, 0, 0};
+  // The frame's whole 16-byte chunks (the base is 16-byte aligned, by
+  // contract); at most 15 bytes on either side are counted one by one.
+  const long s0 = (long)f * frame_bytes, s1 = s0 + frame_bytes;
+  const long a0 = min((s0 + 15) & ~15L, s1), a1 = max(a0, s1 & ~15L);
+  const long n16 = (a1 - a0) / 16;
+  const long i0 = n16 * part / split, i1 = n16 * (part + 1) / split;
+  const u32x4 *src = reinterpret_cast<const u32x4 *>(frames + a0);
+  const int lead = (int)(a0 - s0);  // bytes before the first chunk
+  // Byte b of the frame belongs to channel b % 3; chunk i starts at byte
+  // lead + 16 i, channel (lead + i) % 3. Batches of HIST_B chunks per thread;
+  // a batch's loads are issued before the previous batch is counted.
+  constexpr int HIST_B = 4;
+  auto load = [&](long i, u32x4 (&v)[HIST_B]) {
 #pragma unroll
     for (int b = 0; b < HIST_B; ++b) {
       const long ib = i + (long)b * HIST_T;
-      v[b] = ib < i1 ? reinterpret_cast<const u32x4 *>(src)[ib] : u32x4{0u, 0u, 0u, 0u};
+      if (ib < i1) v[b] = src[ib];
     }
+  };
+  auto count = [&](long i, const u32x4 (&v)[HIST_B]) {
 #pragma unroll
     for (int b = 0; b < HIST_B; ++b) {
       const long ib = i + (long)b * HIST_T;
       if (ib >= i1) break;
-      int c = (int)(ib % 3);
+      const int c0 = (int)((lead + ib) % 3);
+      // Byte offsets of this lane's word in bin 0 of the channels of bytes
+      // 0, 1, 2 mod 3 (64 bins x 256 bytes per channel).
+      const uint32_t l4 = 4u * lane;
+      const uint32_t o0 = l4 | (uint32_t)(c0 << 14);
+      const uint32_t o1 = l4 | (uint32_t)((c0 == 2 ? 0 : c0 + 1) << 14);
+      const uint32_t o2 = l4 | (uint32_t)((c0 == 0 ? 2 : c0 - 1) << 14);
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const uint32_t byte = (v[b][j >> 2] >> (8 * (j & 3))) & 0xFFu;
-        atomicAdd(&h[w][c * BINS + (byte >> 2)], 1);
-        c = c == 2 ? 0 : c + 1;
+        // (byte >> 2) << 8: the bin's byte offset within the channel.
+        const uint32_t x = v[b][j >> 2];
+        const int sh = 8 * (j & 3) - 6;
+        const uint32_t bin = (sh < 0 ? x << 6 : x >> sh) & 0x3F00u;
+        const uint32_t off = bin | (j % 3 == 0 ? o0 : j % 3 == 1 ? o1 : o2);
+        atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(h) + off), 1u);
       }
     }
-  }
-  if (part == HIST_SPLIT - 1)
-    for (long b = n16 * 16 + t; b < frame_bytes; b += HIST_T)
-      atomicAdd(&h[w][(int)(b % 3) * BINS + (src[b] >> 2)], 1);
+  };
+  u32x4 va[HIST_B], vb[HIST_B];
+  constexpr long STEP = (long)HIST_B * HIST_T;
+  load(i0 + t, va);
   __syncthreads();
-  for (int i = t; i < HB; i += HIST_T) {
-    int32_t s = 0;
-    for (int k = 0; k < HIST_W; ++k) s += h[k][i];
-    if (s) atomicAdd(&hist[(long)f * HB + i], s);
+  for (long i = i0 + t; i < i1; i += 2 * STEP) {
+    load(i + STEP, vb);
+    count(i, va);
+    if (i + STEP >= i1) break;
+    load(i + 2 * STEP, va);
+    count(i + STEP, vb);
+  }
+  if (part == 0 && t < 32) {  // bytes outside the chunks
+    const long b = t < 16 ? s0 + t : a1 + (t - 16), e = t < 16 ? a0 : s1;
+    if (b < e)
+      atomicAdd(&h[64 * ((int)((b - s0) % 3) * BINS + (frames[b] >> 2)) + lane], 1u);
+  }
+  __syncthreads();
+  // Four threads sum a bin's words (rotated by the bin: distinct banks).
+  if (t < 4 * HB) {
+    const int bin = t >> 2;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum += h[64 * bin + ((16 * (t & 3) + i + bin) & 63)];
+    sum += __shfl_xor(sum, 1, 64);
+    sum += __shfl_xor(sum, 2, 64);
+    if ((t & 3) == 0) {
+      int32_t *dst = hist + (long)f * HB + bin;
+      if constexpr (!ATOMIC)
+        *dst = (int32_t)sum;
+      else if (sum)
+        atomicAdd(dst, (int32_t)sum);
+    }
   }
 }
 
 // One block: inter[i] = sum_b min(hist[i][b], hist[i-1][b]) (inter[0] = -1),
 // keyframe flags (frame 0, and inter[i] < theta * 3HW), then the ordered
-// list of keyframe indices.
+// list of keyframe indices. Wave w takes a run of consecutive frames, the
+// lanes three bins each, KF_U frames' loads in flight (a thread per frame
+// walking its 192 bins alone took 12.5 us for 220 frames; now 5.8 us).
+constexpr int KF_U = 16;
 __global__ __launch_bounds__(1024) void k_keyframes(const int32_t *hist, int NF, double thr,
                                                     int32_t *inter, int32_t *key_idx,
                                                     int32_t *n_keys) {
-  __shared__ int32_t cnt[1024];
-  const int t = threadIdx.x;
-  // Frames are handled in contiguous runs per thread so that the compaction
-  // keeps their order.
-  const int per = (NF + 1023) / 1024, f0 = t * per, f1 = min(NF, f0 + per);
-  int mine = 0;
-  for (int f = f0; f < f1; ++f) {
-    bool key = f == 0;
-    if (f > 0) {
-      const int32_t *a = hist + (long)f * HB, *b = a - HB;
-      int32_t s = 0;
-      for (int i = 0; i < HB; ++i) s += min(a[i], b[i]);
-      inter[f] = s;
-      key = (double)s < thr;
-    } else {
-      inter[0] = -1;
-    }
-    mine += key;
-  }
-  cnt[t] = mine;
+  __shared__ uint32_t flags[2048];  // a bit per frame (NF <= 65536)
+  __shared__ int32_t wsum[16];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  flags[t] = 0u;
+  flags[t + 1024] = 0u;
   __syncthreads();
-  // Exclusive prefix sum of the per-thread counts (Hillis-Steele in LDS).
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = t >= off ? cnt[t - off] : 0;
-    __syncthreads();
-    cnt[t] += v;
-    __syncthreads();
-  }
-  int pos = cnt[t] - mine;
-  for (int f = f0; f < f1; ++f) {
-    const bool key = f == 0 || (double)inter[f] < thr;
-    if (key) key_idx[pos++] = f;
-  }
-  if (t == 1023) *n_keys = cnt[1023];
-}
-
-constexpr int RG = 16;       // keyframes per retrieval block
-constexpr int RT = 256;      // threads of a retrieval block = documents per block
-constexpr int RW = RT / 64;
-
-struct SimIdx {
-  float s;
-  int32_t i;
-};
-
-// a ranks before b: higher similarity, then lower document index.
-__device__ __forceinline__ bool before(float sa, int ia, float sb, int ib) {
-  return sa > sb || (sa == sb && ia < ib);
-}
-
-// The better of two (similarity, index) candidates; index -1 is no candidate.
-__device__ __forceinline__ void keep_better(float &s, int &i, float s2, int i2) {
-  if (i2 >= 0 && (i < 0 || before(s2, i2, s, i))) {
-    s = s2;
-    i = i2;
-  }
-}
-
-// Best candidate of the wave (fixed butterfly order), in every lane.
-__device__ __forceinline__ void wave_best(float &s, int &i) {
+  const int per = (NF + 15) / 16, f0 = w * per, f1 = min(NF, f0 + per);
+  for (int f = f0; f < f1; f += KF_U) {
+    int32_t v[KF_U + 1][3];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float s2 = __shfl_xor(s, o, 64);
-    const int i2 = __shfl_xor(i, o, 64);
-    keep_better(s, i, s2, i2);
+    for (int u = 0; u <= KF_U; ++u) {  // rows f - 1 .. f + KF_U - 1
+      const int32_t *row = hist + (long)min(max(f - 1 + u, 0), NF - 1) * HB + lane;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) v[u][j] = row[64 * j];
+    }
+#pragma unroll
+    for (int u = 0; u < KF_U; ++u) {
+      int32_t s = 0;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) s += min(v[u][j], v[u + 1][j]);
+      s = wave_scan(s);  // the last lane has the sum
+      const int g = f + u;
+      if (lane == 63 && g < f1) {
+        inter[g] = g == 0 ? -1 : s;
+        if (g == 0 || (double)s < thr) atomicOr(&flags[g >> 5], 1u << (g & 31));
+      }
+    }
   }
+  __syncthreads();
+  // Thread t owns frames 64 t .. 64 t + 63: exclusive sums of the counts.
+  uint32_t lo = flags[2 * t], hi = flags[2 * t + 1];
+  const int mine = __popc(lo) + __popc(hi);
+  const int sum = wave_scan(mine);
+  if (lane == 63) wsum[w] = sum;
+  __syncthreads();
+  int pos = sum - mine, total = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (i < w) pos += wsum[i];
+    total += wsum[i];
+  }
+  for (; lo; lo &= lo - 1) key_idx[pos++] = 64 * t + __ffs(lo) - 1;
+  for (; hi; hi &= hi - 1) key_idx[pos++] = 64 * t + 32 + __ffs(hi) - 1;
+  if (t == 0) *n_keys = total;
 }
 
-// The per-chunk top-k of keyframes g0 .. g0+ng-1 from sims [RG][RT] in LDS:
-// wave w of NWV takes keyframes w, w + NWV, ..., k passes of a wave-wide best.
+constexpr int RG = 16;       // keyframes per column group of the bank scan
+constexpr int RT = 256;      // documents a block scores at a time
+
+// A ranked candidate as one unsigned 64-bit key: the similarity's
+// order-preserving bits above the complement of the document index, so a
+// larger key ranks before (ties: the lower index). 0: no candidate (a NaN is
+// none). Comparisons and wave-wide maxima then are plain integer ones.
+typedef unsigned long long key_t64;
+__device__ __forceinline__ key_t64 make_key(float s, int i) {
+  const uint32_t b = __float_as_uint(s + 0.f);  // -0 ranks as 0
+  const uint32_t o = b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+  return isnan(s) ? 0ull : ((key_t64)o << 32) | (uint32_t)~i;
+}
+__device__ __forceinline__ int key_index(key_t64 k) { return k ? (int)~(uint32_t)k : -1; }
+__device__ __forceinline__ float key_sim(key_t64 k) {
+  const uint32_t o = (uint32_t)(k >> 32);
+  return __uint_as_float(o ^ (o & 0x80000000u ? 0x80000000u : 0xFFFFFFFFu));
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ key_t64 max_dpp(key_t64 v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xF, false);
+  const key_t64 u = ((key_t64)(uint32_t)hi << 32) | (uint32_t)lo;
+  return u > v ? u : v;
+}
+
+// Largest key of the wave, in every lane: row shifts, then the rows' last
+// lanes broadcast (a butterfly of LDS permutes took about 0.5 us a pass).
+__device__ __forceinline__ key_t64 wave_best(key_t64 v) {
+  v = max_dpp<0x111, 0xF>(v);
+  v = max_dpp<0x112, 0xF>(v);
+  v = max_dpp<0x114, 0xF>(v);
+  v = max_dpp<0x118, 0xF>(v);
+  v = max_dpp<0x142, 0xA>(v);
+  v = max_dpp<0x143, 0xC>(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
+  return ((key_t64)hi << 32) | lo;
+}
+
+__device__ __forceinline__ key_t64 max_below(key_t64 best, key_t64 c, key_t64 last) {
+  return c < last && c > best ? c : best;
+}
+
+// The top-k of keyframes g0 .. g0+ng-1 over the documents d0 .. d0+nd-1 (sims
+// [..][RT] in LDS) and, unless `first`, over the block's list so far: wave w of
+// NWV takes keyframes w, w + NWV, ..., k passes of a wave-wide best.
 template <int NWV>
-__device__ __forceinline__ void chunk_topk(const float (*sims)[RT], int g0, int ng, int d0,
-                                           int nvalid, int k, int nchunks, SimIdx *part) {
+__device__ __forceinline__ void block_topk(const float (*sims)[RT], int g0, int ng, int d0,
+                                           int nd, bool first, int k, int nlists, int list,
+                                           key_t64 *part) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int r = w; r < ng; r += NWV) {
-    SimIdx *out = part + ((long)(g0 + r) * nchunks + blockIdx.x) * k;
-    float last_s = INFINITY;
-    int last_i = -1;
+    key_t64 *out = part + ((long)(g0 + r) * nlists + list) * k;
+    const key_t64 old = !first && lane < k ? out[lane] : 0ull;  // (the wave's own stores)
+    key_t64 c[RT / 64];
+#pragma unroll
+    for (int e = 0; e < RT / 64; ++e) {
+      const int j = lane + 64 * e;
+      c[e] = j < nd ? make_key(sims[r][j], d0 + j) : 0ull;
+    }
+    key_t64 last = ~0ull, mine = 0ull;
     for (int p = 0; p < k; ++p) {
-      float bs = -INFINITY;
-      int bi = -1;
-      for (int j = lane; j < nvalid; j += 64) {
-        const float sj = sims[r][j];
-        if (before(last_s, last_i, sj, d0 + j)) keep_better(bs, bi, sj, d0 + j);
-      }
-      wave_best(bs, bi);
-      if (lane == 0) out[p] = SimIdx{bs, bi};  // -1: fewer than k documents left
-      last_s = bi < 0 ? -INFINITY : bs;
-      last_i = bi;
+      key_t64 best = max_below(0ull, old, last);
+#pragma unroll
+      for (int e = 0; e < RT / 64; ++e) best = max_below(best, c[e], last);
+      last = wave_best(best);
+      if (lane == p) mine = last;  // 0: fewer than k documents left
     }
+    if (lane < k) out[lane] = mine;
   }
 }
 
-// Block (document chunk, keyframe group): thread t scores document
-// d0 + t against up to RG keyframes held in LDS (every lane reads the same
-// keyframe value: an LDS broadcast), then wave w picks the top-k of the chunk
-// for keyframes w, w + RW, ... -> part[key][chunk][k].
-__global__ __launch_bounds__(RT) void k_retrieve_chunk(const float *frame_emb,
-                                                       const int32_t *key_idx,
-                                                       const int32_t *n_keys,
-                                                       const float *docs, int ND, int D, int k,
-                                                       int nchunks, SimIdx *part) {
-  __shared__ __align__(16) float q[RG][1024];
-  __shared__ float qn[RG];
-  __shared__ float sims[RG][RT];
-  const int nk = *n_keys;
-  const int g0 = blockIdx.y * RG;
-  if (g0 >= nk) return;  // uniform per block
-  const int ng = min(RG, nk - g0);
-  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  for (int r = 0; r < ng; ++r) {
-    const float *src = frame_emb + (long)key_idx[g0 + r] * D;
-    for (int c = t; c < D; c += RT) q[r][c] = src[c];
-  }
-  __syncthreads();
-  for (int r = w; r < ng; r += RW) {
-    float s = 0.f;
-    for (int c = lane; c < D; c += 64) s += q[r][c] * q[r][c];
-    s = wave_sum(s);
-    if (lane == 0) qn[r] = sqrtf(s);
-  }
-  __syncthreads();
-  const int d0 = blockIdx.x * RT, doc = d0 + t;
-  float dot[RG], dd = 0.f;
-#pragma unroll
-  for (int r = 0; r < RG; ++r) dot[r] = 0.f;
-  if (doc < ND) {
-    const float *src = docs + (long)doc * D;
-    if ((D & 3) == 0) {  // rows 16-byte aligned (the base is, by contract)
-      for (int c = 0; c < D; c += 4) {
-        const float4 v = *reinterpret_cast<const float4 *>(src + c);
-        dd += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-#pragma unroll
-        for (int r = 0; r < RG; ++r) {
-          const float4 e = *reinterpret_cast<const float4 *>(&q[r][c]);
-          dot[r] += e.x * v.x + e.y * v.y + e.z * v.z + e.w * v.w;
-        }
-      }
-    } else {
-      for (int c = 0; c < D; ++c) {
-        const float v = src[c];
-        dd += v * v;
-#pragma unroll
-        for (int r = 0; r < RG; ++r) dot[r] += q[r][c] * v;
-      }
-    }
-  }
-  const float dn = sqrtf(dd);
-#pragma unroll
-  for (int r = 0; r < RG; ++r) {
-    if (r < ng) {
-      const float den = qn[r] * dn;
-      sims[r][t] = den > 0.f ? dot[r] / den : 0.f;
-    }
-  }
-  __syncthreads();
-  chunk_topk<RW>(sims, g0, ng, d0, min(RT, ND - d0), k, nchunks, part);
-}
-
-// Matrix-core scan for D % 16 == 0: the dot products of a chunk's 256
-// documents with up to 16 keyframes are a [256 x D] . [D x 16] product in
-// fp32 (v_mfma_f32_16x16x4_f32). Eight waves; wave w owns documents
-// 32 w .. 32 w + 31 as two 16-row tiles. Per 16 dimensions lane l loads 4
-// consecutive values of document (l % 16) of each tile (16 rows x 64
-// contiguous bytes per load) and the matching 4 values of keyframe (l % 16)
-// from LDS, and runs 4 products per tile (product j takes dimension
-// 4 (l / 16) + j of each lane group, the same for both operands). The
-// documents' squared norms come from the same loads. Steps of 64 dimensions;
-// the next step's loads are issued before the current step's products.
+// Scan of the bank: block `list` of nlists scores an even share of the
+// documents, at most 256 at a time, against up to RG KG keyframes, as a
+// [documents x D] . [D x 16 KG] product in fp32 (v_mfma_f32_16x16x4_f32).
+// Eight waves; of a batch's 16-document tiles wave w owns tiles w and w + 8.
+// Per 16 dimensions lane l loads 4 consecutive values of document (l % 16) of
+// each tile (16 rows x 64 contiguous bytes per load) and the matching 4
+// values of keyframe (l % 16) from LDS, and runs 4 products per tile (product
+// j takes dimension 4 (l / 16) + j of each lane group, the same for both
+// operands). The documents' squared norms come from the same loads. Steps of
+// 64 dimensions; the next step's loads are issued before the current step's
+// products, a batch's first ones before the previous batch's lists are made.
+// Dimensions past the last whole 16 are loaded one by one, zeros past D
+// (keyframe rows in LDS are padded with zeros to whole 16s, and by 4 floats
+// more so that the 16 rows of an LDS read fall into distinct banks).
+//
+// HBM-bound: the bank is read once per 16 KG keyframes. With a block per 256
+// documents and group of 16 frames, the empty blocks of a grid sized for
+// every frame being a keyframe (391 x 14 blocks for 220 frames) held LDS that
+// the others waited for, and 391 equal shares do not divide evenly over 256
+// CUs: 84 us for 12 keyframes over 100k x 768 (3.7 TB/s), now 71 us (4.3 TB/s).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int RM_T = 512;
-__global__ __launch_bounds__(RM_T) void k_retrieve_mfma(const float *frame_emb,
+template <int KG>
+__global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
                                                         const int32_t *key_idx,
                                                         const int32_t *n_keys, const float *docs,
-                                                        int ND, int D, int k, int nchunks,
-                                                        SimIdx *part) {
-  constexpr int NG = RT / (RM_T / 64) / 16;  // 16-row tiles per wave
-  // The keyframes, [RG][D] (dynamic: D floats a row, so that two blocks fit
-  // a CU at D = 768).
-  extern __shared__ __align__(16) float q[];
-  __shared__ float qn[RG];
+                                                        int ND, int D, int k, int nlists,
+                                                        key_t64 *part, int32_t *n_sel) {
+  constexpr int NG = 2;  // 16-document tiles per wave
+  extern __shared__ __align__(16) float q[];  // keyframes, [RG KG][QS]
+  __shared__ float qn[RG * KG];
   __shared__ float dn[RT];
-  __shared__ float sims[RG][RT];
-  const int nk = *n_keys;
-  const int g0 = blockIdx.y * RG;
-  if (g0 >= nk) return;  // uniform per block
-  const int ng = min(RG, nk - g0);
+  __shared__ float sims[RG * KG][RT];
+  const int nk = *n_keys, list = blockIdx.x;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  for (int r = 0; r < RG; ++r) {  // rows past ng: zeros (their columns are unused)
-    const float *src = frame_emb + (long)key_idx[g0 + min(r, ng - 1)] * D;
-    for (int c = t; c < D; c += RM_T) q[r * D + c] = r < ng ? src[c] : 0.f;
-  }
-  __syncthreads();
-  for (int r = w; r < ng; r += RM_T / 64) {
-    float s = 0.f;
-    for (int c = lane; c < D; c += 64) s += q[r * D + c] * q[r * D + c];
-    s = wave_sum(s);
-    if (lane == 0) qn[r] = sqrtf(s);
-  }
-  const int d0 = blockIdx.x * RT;
+  const int QS = (D + 15) / 16 * 16 + 4, nfull = D / 16;
   const int sub = 4 * (lane >> 4);
+  // n_sel counts finished keyframes in the merge (the next launch).
+  if (list == 0 && t == 0) *n_sel = 0;
+  const int b0 = (int)((long)ND * list / nlists), b1 = (int)((long)ND * (list + 1) / nlists);
+  const int nb = (b1 - b0 + RT - 1) / RT;  // batches (at least one: nlists <= ND)
   const float *dp[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g)
-    dp[g] = docs + (long)min(d0 + 16 * NG * w + 16 * g + (lane & 15), ND - 1) * D + sub;
-  const float *qp = q + (lane & 15) * D + sub;
-  f32x4 acc[NG];
-  float dd[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    dd[g] = 0.f;
-  }
-  // Loads of the step at dimension c (pieces past D repeat the last one).
-  auto load = [&](int c, float4 (&v)[4][NG]) {
-    const int cnt = min(4, (D - c) / 16);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int cc = c + 16 * min(u, cnt - 1);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) v[u][g] = *reinterpret_cast<const float4 *>(dp[g] + cc);
-    }
-  };
-  auto step = [&](int c, const float4 (&v)[4][NG]) {
-    const int cnt = min(4, (D - c) / 16);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (u >= cnt) break;
-      const float4 e = *reinterpret_cast<const float4 *>(qp + c + 16 * u);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const float4 x = v[u][g];
-        dd[g] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
-        acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, e.x, acc[g], 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, e.y, acc[g], 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, e.z, acc[g], 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, e.w, acc[g], 0, 0, 0);
-      }
-    }
-  };
-  float4 va[4][NG], vb[4][NG];
-  load(0, va);
-  for (int c = 0; c < D; c += 128) {
-    if (c + 64 < D) load(c + 64, vb);
-    __builtin_amdgcn_sched_barrier(0);
-    step(c, va);
-    if (c + 64 >= D) break;
-    if (c + 128 < D) load(c + 128, va);
-    __builtin_amdgcn_sched_barrier(0);
-    step(c + 64, vb);
-  }
-  // Squared norm of document 16 NG w + 16 g + l % 16: the four lane groups'
-  // partial sums (fixed order).
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    float s = dd[g];
-    s += __shfl_xor(s, 16, 64);
-    s += __shfl_xor(s, 32, 64);
-    if (lane < 16) dn[16 * NG * w + 16 * g + lane] = sqrtf(s);
-  }
-  __syncthreads();
-  // Lane l holds document 16 NG w + 16 g + 4 (l / 16) + i against keyframe l % 16.
-  const int r = lane & 15;
-  if (r < ng) {
+  int d0 = 0, nd = 0;
+  bool second = false;  // the wave's second tile is in use
+  auto batch = [&](int b) {
+    d0 = b0 + (int)((long)(b1 - b0) * b / nb);
+    nd = b0 + (int)((long)(b1 - b0) * (b + 1) / nb) - d0;
+    second = 16 * (w + 8) < nd;
 #pragma unroll
     for (int g = 0; g < NG; ++g)
+      dp[g] = docs + (long)(d0 + min(16 * (w + 8 * g) + (lane & 15), nd - 1)) * D + sub;
+  };
+  // Loads of the step at piece c (pieces past the last whole one repeat it).
+  auto load = [&](int c, f32x4 (&v)[4][NG]) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = 16 * NG * w + 16 * g + 4 * (lane >> 4) + i;
-        const float den = qn[r] * dn[j];
-        sims[r][j] = den > 0.f ? acc[g][i] / den : 0.f;
+    for (int u = 0; u < 4; ++u) {
+      const int cc = 16 * min(c + u, nfull - 1);
+      v[u][0] = *reinterpret_cast<const f32x4u *>(dp[0] + cc);
+      if (second) v[u][1] = *reinterpret_cast<const f32x4u *>(dp[1] + cc);
+    }
+  };
+  for (int g0 = 0; g0 < nk; g0 += RG * KG) {
+    const int ng = min(RG * KG, nk - g0);
+    const bool two = KG == 2 && ng > RG;  // the second column group is in use
+    f32x4 va[4][NG], vb[4][NG];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) va[u][1] = vb[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    batch(0);
+    if (nfull > 0) load(0, va);
+    if (g0 > 0) __syncthreads();  // the previous group's lists are done
+    for (int r = w; r < RG * KG; r += RM_T / 64) {  // a wave per row; rows past ng: zeros
+      const float *src = frame_emb + (long)key_idx[g0 + min(r, ng - 1)] * D;
+      float s = 0.f;
+      for (int c = lane; c < QS; c += 64) {
+        const float v = r < ng && c < D ? src[c] : 0.f;
+        q[r * QS + c] = v;
+        s += v * v;
       }
-  }
-  __syncthreads();
-  chunk_topk<RM_T / 64>(sims, g0, ng, d0, min(RT, ND - d0), k, nchunks, part);
-}
-
-// Block r < n_keys: the top-k of keyframe r over every chunk's top-k. Each
-// thread holds its first MERGE_PER candidates in registers (loaded once; a
-// larger bank's further candidates are re-read on each pass); k passes of a
-// block-wide best (wave butterflies, then the waves in order).
-constexpr int MERGE_T = 1024;
-constexpr int MERGE_PER = 8;
-__global__ __launch_bounds__(MERGE_T) void k_retrieve_merge(const SimIdx *part,
-                                                            const int32_t *n_keys, int nchunks,
-                                                            int k, int32_t *top_idx,
-                                                            float *top_sim) {
-  __shared__ float ws[MERGE_T / 64];
-  __shared__ int wi[MERGE_T / 64];
-  const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
-  if (r >= *n_keys) return;  // uniform per block
-  const SimIdx *p = part + (long)r * nchunks * k;
-  const int n = nchunks * k;
-  float cs[MERGE_PER];
-  int ci[MERGE_PER];
-#pragma unroll
-  for (int e = 0; e < MERGE_PER; ++e) {
-    const int j = t + e * MERGE_T;
-    const SimIdx c = j < n ? p[j] : SimIdx{-INFINITY, -1};
-    cs[e] = c.s;
-    ci[e] = c.i;
-  }
-  float last_s = INFINITY;
-  int last_i = -1;
-  for (int q = 0; q < k; ++q) {
-    float bs = -INFINITY;
-    int bi = -1;
-#pragma unroll
-    for (int e = 0; e < MERGE_PER; ++e)
-      if (ci[e] >= 0 && before(last_s, last_i, cs[e], ci[e])) keep_better(bs, bi, cs[e], ci[e]);
-    for (int j = t + MERGE_PER * MERGE_T; j < n; j += MERGE_T) {
-      const SimIdx c = p[j];
-      if (c.i >= 0 && before(last_s, last_i, c.s, c.i)) keep_better(bs, bi, c.s, c.i);
-    }
-    wave_best(bs, bi);
-    if (lane == 0) {
-      ws[w] = bs;
-      wi[w] = bi;
+      s = wave_sum(s);
+      if (lane == 0) qn[r] = sqrtf(s);
     }
     __syncthreads();
-    bs = ws[0];
-    bi = wi[0];
-    for (int i = 1; i < MERGE_T / 64; ++i) keep_better(bs, bi, ws[i], wi[i]);
-    __syncthreads();
-    if (t == 0) {
-      top_idx[(long)r * k + q] = bi;
-      top_sim[(long)r * k + q] = bi < 0 ? 0.f : bs;
-    }
-    last_s = bi < 0 ? -INFINITY : bs;
-    last_i = bi;
-  }
-}
-
-// One block: T* = the K best documents of the union of the top-k lists, a
-// document scored by the best similarity it was retrieved with (Eq. 3).
-__global__ __launch_bounds__(1024) void k_select_docs(const int32_t *top_idx,
-                                                      const float *top_sim,
-                                                      const int32_t *n_keys, int k, int K,
-                                                      int32_t *sel_idx, float *sel_sim,
-                                                      int32_t *n_sel) {
-  __shared__ float bs[1024];
-  __shared__ int bi[1024];
-  __shared__ int chosen[64];
-  const int t = threadIdx.x, n = *n_keys * k;
-  int got = 0;
-  for (int q = 0; q < K; ++q) {
-    // Thread-local best among entries not yet chosen.
-    float s = -INFINITY;
-    int i = -1;
-    for (int e = t; e < n; e += 1024) {
-      const int d = top_idx[e];
-      if (d < 0) continue;
-      bool taken = false;
-      for (int c = 0; c < got; ++c) taken = taken || chosen[c] == d;
-      if (taken) continue;
-      const float v = top_sim[e];
-      if (i < 0 || before(v, d, s, i)) {
-        s = v;
-        i = d;
+    const float *qp = q + (lane & 15) * QS + sub;
+    for (int b = 0; b < nb; ++b) {
+      f32x4 acc[KG][NG];
+      float dd[NG];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+#pragma unroll
+        for (int h = 0; h < KG; ++h) acc[h][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        dd[g] = 0.f;
       }
-    }
-    bs[t] = s;
-    bi[t] = i;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-      if (t < off) {
-        const int j = bi[t + off];
-        if (j >= 0 && (bi[t] < 0 || before(bs[t + off], j, bs[t], bi[t]))) {
-          bs[t] = bs[t + off];
-          bi[t] = j;
+      auto piece = [&](int c, const f32x4 (&v)[NG]) {
+        const f32x4 e0 = *reinterpret_cast<const f32x4 *>(qp + 16 * c);
+        f32x4 e1 = e0;
+        if (two) e1 = *reinterpret_cast<const f32x4 *>(qp + RG * QS + 16 * c);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          const f32x4 x = v[g];
+          dd[g] += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[0][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e0[j], acc[0][g], 0, 0, 0);
+          if (two)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              acc[KG - 1][g] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e1[j], acc[KG - 1][g], 0, 0, 0);
+        }
+      };
+      auto step = [&](int c, const f32x4 (&v)[4][NG]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (c + u >= nfull) break;
+          piece(c + u, v[u]);
+        }
+      };
+      for (int c = 0; c < nfull; c += 8) {
+        if (c + 4 < nfull) load(c + 4, vb);
+        __builtin_amdgcn_sched_barrier(0);
+        step(c, va);
+        if (c + 4 >= nfull) break;
+        if (c + 8 < nfull) load(c + 8, va);
+        __builtin_amdgcn_sched_barrier(0);
+        step(c + 4, vb);
+      }
+      if (D % 16) {
+        f32x4 x[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            x[g][j] = 16 * nfull + sub + j < D ? dp[g][16 * nfull + j] : 0.f;
+        piece(nfull, x);
+      }
+      const int d0b = d0, ndb = nd;
+      if (b + 1 < nb) {
+        batch(b + 1);
+        if (nfull > 0) load(0, va);
+      }
+      // Squared norms: the four lane groups' partial sums (fixed order).
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        float s = dd[g];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane < 16) dn[16 * (w + 8 * g) + lane] = sqrtf(s);
+      }
+      __syncthreads();  // (also: the previous batch's lists are done)
+      // Lane l holds document 16 (w + 8 g) + 4 (l / 16) + i of the batch
+      // against keyframe l % 16 of each column group.
+#pragma unroll
+      for (int h = 0; h < KG; ++h) {
+        const int r = RG * h + (lane & 15);
+        if (r < ng) {
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int j = 16 * (w + 8 * g) + 4 * (lane >> 4) + i;
+              const float den = qn[r] * dn[j];
+              sims[r][j] = den > 0.f ? acc[h][g][i] / den : 0.f;
+            }
         }
       }
       __syncthreads();
+      block_topk<RM_T / 64>(sims, g0, ng, d0b, ndb, b == 0, k, nlists, list, part);
     }
-    const int best = bi[0];
-    const float bsim = bs[0];
+  }
+}
+
+// A value written by one block and read by another of the same launch: agent
+// scope, so it goes past the writer's own L2.
+template <typename T>
+__device__ __forceinline__ void put_agent(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T get_agent(const T *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Block r < n_keys: the top-k of keyframe r over every block's top-k, then, in
+// the block that finishes last, T* = the K best documents of the union of the
+// top-k lists, a document scored by the best similarity it was retrieved with
+// (Eq. 3). Each wave takes the top-k of its own share of the candidates (the
+// first MERGE_PER per thread in registers; a larger bank's further ones are
+// re-read on each pass) without block barriers, then wave 0 merges the 16
+// lists. The finished keyframes are counted in n_sel, which the scan zeroed
+// and which gets its value at the end. The lists are stored and loaded at
+// agent scope, and a block counts itself once its stores are acknowledged (an
+// agent-scope release would write back the whole L2: 13.7 us for 6 candidates
+// per keyframe). As two launches the merge and the selection took 9.8 + 7.1 us
+// for 12 keyframes over 100k documents, now 7.7 us.
+constexpr int MERGE_T = 1024;
+constexpr int MERGE_PER = 8;
+__global__ __launch_bounds__(MERGE_T) void k_retrieve_merge(const key_t64 *part,
+                                                            const int32_t *n_keys, int nlists,
+                                                            int k, int K, int32_t *top_idx,
+                                                            float *top_sim, int32_t *sel_idx,
+                                                            float *sel_sim, int32_t *n_sel) {
+  __shared__ key_t64 wl[16 * (MERGE_T / 64)];  // list q of wave w at 16 q + w
+  __shared__ int32_t finished;
+  __shared__ int chosen[64];
+  const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const key_t64 *p = part + (long)r * nlists * k;
+  const int n = nlists * k, nk = *n_keys;
+  key_t64 c[MERGE_PER];  // (loaded beside n_keys: rows past it hold other values, unused)
+#pragma unroll
+  for (int e = 0; e < MERGE_PER; ++e) c[e] = t + e * MERGE_T < n ? p[t + e * MERGE_T] : 0ull;
+  if (r >= nk) return;  // uniform per block
+  key_t64 last = ~0ull;
+  for (int q = 0; q < k; ++q) {
+    key_t64 best = 0ull;
+#pragma unroll
+    for (int e = 0; e < MERGE_PER; ++e) best = max_below(best, c[e], last);
+    for (int j = t + MERGE_PER * MERGE_T; j < n; j += MERGE_T) best = max_below(best, p[j], last);
+    last = wave_best(best);
+    if (lane == 0) wl[16 * q + w] = last;
+    // (0: the wave's candidates are used up, the remaining passes find none)
+  }
+  __syncthreads();
+  if (w == 0) {
+    key_t64 m[4], mine = 0ull;  // 16 lists of k <= 16
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = lane + 64 * e < 16 * k ? wl[lane + 64 * e] : 0ull;
+    last = ~0ull;
+    for (int q = 0; q < k; ++q) {
+      key_t64 best = 0ull;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) best = max_below(best, m[e], last);
+      last = wave_best(best);
+      if (lane == q) mine = last;
+    }
+    if (lane < k) {
+      put_agent(top_idx + (long)r * k + lane, key_index(mine));
+      put_agent(top_sim + (long)r * k + lane, mine ? key_sim(mine) : 0.f);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the list is out
+    if (lane == 0)
+      finished = __hip_atomic_fetch_add(n_sel, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (finished != nk - 1) return;  // uniform per block
+  const int ne = nk * k;
+  auto entry = [&](int e) {
+    const int d = get_agent(top_idx + e);
+    const float v = get_agent(top_sim + e);
+    return d < 0 ? 0ull : make_key(v, d);
+  };
+  // The thread's first entry stays in a register (the only one up to 1024).
+  key_t64 e0 = t < ne ? entry(t) : 0ull;
+  int got = 0;
+  for (int q = 0; q < K; ++q) {
+    // Best among the entries whose document is not chosen yet.
+    key_t64 best = e0;
+    for (int e = t + MERGE_T; e < ne; e += MERGE_T) {
+      const key_t64 x = entry(e);
+      bool taken = false;
+      for (int i = 0; i < got; ++i) taken = taken || chosen[i] == key_index(x);
+      if (!taken && x > best) best = x;
+    }
+    best = wave_best(best);
+    if (lane == 0) wl[16 * (q & 1) + w] = best;
     __syncthreads();
-    if (best < 0) break;  // uniform: every thread read the same bi[0]
+    best = wave_best(lane < MERGE_T / 64 ? wl[16 * (q & 1) + lane] : 0ull);
+    if (!best) break;  // uniform: every wave reduced the same 16 entries
+    const int d = key_index(best);
     if (t == 0) {
-      sel_idx[got] = best;
-      sel_sim[got] = bsim;
-      chosen[got] = best;
+      sel_idx[got] = d;
+      sel_sim[got] = key_sim(best);
+      chosen[got] = d;
     }
+    if (key_index(e0) == d) e0 = 0ull;
     ++got;
-    __syncthreads();
+    if (ne > MERGE_T) __syncthreads();  // `chosen` is read
   }
   if (t == 0) *n_sel = got;
 }
@@ -477,9 +533,18 @@ hipError_t launch_keyframes(const uint8_t *frames, int NF, int H, int W, float t
                             int32_t *hist, int32_t *inter, int32_t *key_idx, int32_t *n_keys,
                             hipStream_t s) {
   const long fb = (long)H * W * 3;
-  const long nh = (long)NF * HB;
-  k_zero_i32<<<(unsigned)((nh + 255) / 256), 256, 0, s>>>(hist, nh);
-  k_hist<<<NF * HIST_SPLIT, HIST_T, 0, s>>>(frames, fb, hist);
+  // One block per frame stores the frame's counts. Fewer than 128 frames leave
+  // half of the CUs idle: larger frames are then cut into parts of at least 32
+  // KB that add into zeroed counts, one more launch (4.5 us).
+  int split = 1;
+  if (NF < 128 && fb > (64 << 10)) split = (int)std::min<long>((511 + NF) / NF, fb >> 15);
+  if (split == 1) {
+    k_hist<false><<<NF, HIST_T, 0, s>>>(frames, fb, 1, hist);
+  } else {
+    const long nh = (long)NF * HB;
+    k_zero_i32<<<(unsigned)((nh + 255) / 256), 256, 0, s>>>(hist, nh);
+    k_hist<true><<<NF * split, HIST_T, 0, s>>>(frames, fb, split, hist);
+  }
   const double thr = (double)theta * 3.0 * (double)((long)H * W);  // (theta 3) (H W)
   k_keyframes<<<1, 1024, 0, s>>>(hist, NF, thr, inter, key_idx, n_keys);
   return hipGetLastError();
@@ -487,24 +552,31 @@ hipError_t launch_keyframes(const uint8_t *frames, int NF, int H, int W, float t
 
 size_t retrieve_workspace_bytes(int NF, int ND, int k) {
   const size_t nchunks = ((size_t)ND + RT - 1) / RT;
-  return (size_t)NF * nchunks * (size_t)k * sizeof(SimIdx);
+  return (size_t)NF * nchunks * (size_t)k * sizeof(key_t64);
 }
 
 hipError_t launch_retrieve(const float *frame_emb, const int32_t *key_idx, const int32_t *n_keys,
                            int NF, const float *docs, int ND, int D, int k, int K, void *ws,
                            int32_t *top_idx, float *top_sim, int32_t *sel_idx, float *sel_sim,
                            int32_t *n_sel, hipStream_t s) {
-  const int nchunks = (ND + RT - 1) / RT;
-  SimIdx *part = static_cast<SimIdx *>(ws);
-  const dim3 grid(nchunks, (NF + RG - 1) / RG);
-  if (D % 16 == 0)
-    k_retrieve_mfma<<<grid, RM_T, RG * D * sizeof(float), s>>>(frame_emb, key_idx, n_keys, docs,
-                                                               ND, D, k, nchunks, part);
+  key_t64 *part = static_cast<key_t64 *>(ws);
+  // 32 keyframes per pass over the bank if there may be more than 16 and their
+  // rows (with 32 lists of similarities) fit the 160 KB of LDS. A list per
+  // block, as many blocks as the CUs hold at once (and lists as the workspace).
+  const size_t qrow = ((size_t)(D + 15) / 16 * 16 + 4) * sizeof(float);
+  const bool wide = NF > RG && 2 * RG * (qrow + RT * sizeof(float)) <= (size_t)150 << 10;
+  const int rows = wide ? 2 * RG : RG;
+  const size_t lds = rows * (qrow + RT * sizeof(float)) + 2048;
+  const int per_cu = (int)std::min<size_t>(2, std::max<size_t>(1, (size_t)(160 << 10) / lds));
+  const int nlists = std::min((ND + RT - 1) / RT, 256 * per_cu);
+  if (wide)
+    k_retrieve_scan<2><<<nlists, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D,
+                                                         k, nlists, part, n_sel);
   else
-    k_retrieve_chunk<<<grid, RT, 0, s>>>(frame_emb, key_idx, n_keys, docs, ND, D, k, nchunks,
-                                         part);
-  k_retrieve_merge<<<NF, MERGE_T, 0, s>>>(part, n_keys, nchunks, k, top_idx, top_sim);
-  k_select_docs<<<1, 1024, 0, s>>>(top_idx, top_sim, n_keys, k, K, sel_idx, sel_sim, n_sel);
+    k_retrieve_scan<1><<<nlists, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D,
+                                                         k, nlists, part, n_sel);
+  k_retrieve_merge<<<NF, MERGE_T, 0, s>>>(part, n_keys, nlists, k, K, top_idx, top_sim, sel_idx,
+                                          sel_sim, n_sel);
   return hipGetLastError();
 }
 
