@@ -959,13 +959,16 @@ __global__ __launch_bounds__(NT) void k_gemm_qkv(const f16 *__restrict__ A,
 }
 
 // Tail tiles: the partials summed in split order, then the rotary and the
-// staged stores as above. Block (tail tile, 64-row quarter), 4 waves: wave w
-// sums head h = w % 2 of the pair for the 4-row groups g = 2 it + w / 2
-// (it < 8), then stores its half of that head's staging block.
+// staged stores as above. Block (tail tile, 64-row quarter), 16 waves: wave w
+// sums head h = w % 2 of the pair for the 4-row groups g = w / 2 and w / 2 + 8,
+// then stores its eighth of that head's staging block. Bound by the round
+// trips of the partial loads: with 4 waves of 8 groups each the few blocks of
+// a short launch (144 at 512 rows of the 7B shape) took 29 us for 66 MB, now
+// QKVR_FIG.
 template <int NS>
-__global__ __launch_bounds__(256) void k_reduce_qkv(const float *__restrict__ part, Launch ln,
-                                                    int rows, int n_heads, int n_kv,
-                                                    QKVOut<f16> o) {
+__global__ __launch_bounds__(1024) void k_reduce_qkv(const float *__restrict__ part, Launch ln,
+                                                     int rows, int n_heads, int n_kv,
+                                                     QKVOut<f16> o) {
   __shared__ u32x4 lds[2 * 1024];  // a 16 KB staging block per head
   const int i = blockIdx.x >> 2, quarter = blockIdx.x & 3;
   int tm, tn;
@@ -979,25 +982,25 @@ __global__ __launch_bounds__(256) void k_reduce_qkv(const float *__restrict__ pa
   VtBlock vb;
   const bool staged = live && !precise &&
                       (value ? vt_block(o, n_heads, n_kv, slot, r0, rows, vb) : qk_staged_ok(o));
-  // The rotary entries of the thread's 32 rows, loaded before the loop (in
-  // it they waited out two memory round trips per row group: the position,
-  // then the entry).
-  float2 cs[8][4];
+  // The rotary entries of the thread's 8 rows, loaded beside the partials (in
+  // the loop below they waited out two memory round trips per row group: the
+  // position, then the entry).
+  float2 cs[2][4];
   if (live && !value) {
-    int pos[8][4];
+    int pos[2][4];
 #pragma unroll
-    for (int it = 0; it < 8; ++it)
+    for (int it = 0; it < 2; ++it)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        pos[it][j] = qkv_row_pos(o, min(r0 + 4 * (2 * it + (w >> 1)) + j, rows - 1));
+        pos[it][j] = qkv_row_pos(o, min(r0 + 4 * (8 * it + (w >> 1)) + j, rows - 1));
 #pragma unroll
-    for (int it = 0; it < 8; ++it)
+    for (int it = 0; it < 2; ++it)
 #pragma unroll
       for (int j = 0; j < 4; ++j) cs[it][j] = o.rope[(long)pos[it][j] * 64 + d];
   }
 #pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int g = 2 * it + (w >> 1);
+  for (int it = 0; it < 2; ++it) {
+    const int g = 8 * it + (w >> 1);
     float x1[4], x2[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1036,9 +1039,9 @@ __global__ __launch_bounds__(256) void k_reduce_qkv(const float *__restrict__ pa
   __syncthreads();
   if (!staged) return;
   if (value)
-    vt_copy_out<8>(stg, vb.vt, vb.npos, vb.crow0, 8 * (w >> 1));
+    vt_copy_out<2>(stg, vb.vt, vb.npos, vb.crow0, 2 * (w >> 1));
   else
-    qk_copy_out<8>(stg, o, n_heads, slot, r0, rows, 8 * (w >> 1));
+    qk_copy_out<2>(stg, o, n_heads, slot, r0, rows, 2 * (w >> 1));
 }
 
 // ------------------------------------------------------ LM head + chunk LSE
@@ -1368,7 +1371,7 @@ hipError_t gemm_qkv_rope(const f16 *A, const void *W, bool w_f16, int rows, int 
                                 K / BK * asplit);
   VSR_WLAUNCH(k_gemm_qkv, ln.blocks(), A, W16, rows, K, asplit, n_heads, n_kv, ln, out, part);
   if (ln.ntail > 0)
-    VSR_REDUCE_LAUNCH(ln.nsplit, k_reduce_qkv, ln.ntail * 4, 256, part, ln, rows, n_heads, n_kv,
+    VSR_REDUCE_LAUNCH(ln.nsplit, k_reduce_qkv, ln.ntail * 4, 1024, part, ln, rows, n_heads, n_kv,
                       out);
   return hipGetLastError();
 }
