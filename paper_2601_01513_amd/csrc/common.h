@@ -36,35 +36,32 @@ template <> __device__ __forceinline__ f16 from_f32<f16>(float x) { return stati
 // Largest number of candidates one score call may carry.
 constexpr int kMaxCands = 256;
 
-// Sum / maximum over the 64 lanes of a wave (fixed order), the result in every
-// lane. Row shifts and broadcasts within the vector ALU; a butterfly of
-// __shfl_xor is six dependent LDS permutes, about 0.2 us, which showed in every
-// small latency-bound kernel.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f32(float old, float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL,
-                                                    ROWS, 0xF, false));
+// Sum / maximum over the 64 lanes of a wave, the result in every lane: lanes
+// 32, 16, 8, 4, 2 and 1 apart in turn (the tree of a __shfl_xor butterfly, bit
+// for bit), by lane swaps and row rotations within the vector ALU. The
+// butterfly itself is six dependent LDS permutes, about 0.2 us, which showed in
+// every small latency-bound kernel.
+template <int CTRL>
+__device__ __forceinline__ float row_rotated(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ float lane63(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  v = op(v, row_rotated<0x128>(v));
+  v = op(v, row_rotated<0x124>(v));
+  v = op(v, row_rotated<0x122>(v));
+  return op(v, row_rotated<0x121>(v));
 }
 __device__ __forceinline__ float wave_sum(float v) {
-  v += dpp_f32<0x111, 0xF>(0.f, v);  // row_shr 1, 2, 4, 8: lane 15 of each row has its sum
-  v += dpp_f32<0x112, 0xF>(0.f, v);
-  v += dpp_f32<0x114, 0xF>(0.f, v);
-  v += dpp_f32<0x118, 0xF>(0.f, v);
-  v += dpp_f32<0x142, 0xA>(0.f, v);  // row_bcast 15 into rows 1 and 3
-  v += dpp_f32<0x143, 0xC>(0.f, v);  // row_bcast 31 into rows 2 and 3
-  return lane63(v);
+  return wave_reduce(v, [](float x, float y) { return x + y; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, dpp_f32<0x111, 0xF>(v, v));  // lanes without a source keep their own
-  v = fmaxf(v, dpp_f32<0x112, 0xF>(v, v));
-  v = fmaxf(v, dpp_f32<0x114, 0xF>(v, v));
-  v = fmaxf(v, dpp_f32<0x118, 0xF>(v, v));
-  v = fmaxf(v, dpp_f32<0x142, 0xA>(v, v));
-  v = fmaxf(v, dpp_f32<0x143, 0xC>(v, v));
-  return lane63(v);
+  return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); });
 }
 
 // Inclusive prefix sum over the lanes of a wave.
@@ -368,6 +365,11 @@ hipError_t skinny_qkv_rope(const f16 *A, int rows, int asplit, const void *W, bo
 int skinny_lm_chunks(int vocab);
 hipError_t skinny_lmargmax(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
                            float2 *part, hipStream_t s);
+// LM head of few rows as gemm_lmhead, in skinny_lse_chunks(vocab) equal chunks
+// (0: not supported).
+int skinny_lse_chunks(int vocab);
+hipError_t skinny_lmhead(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
+                         const int32_t *lm_tgt, float2 *part, float *tgt_logit, hipStream_t s);
 // dst[i] = fp16 of the bf16 src[i], the GEMMs' in-register conversion.
 hipError_t convert_bf16_to_f16(const uint16_t *src, uint16_t *dst, size_t n, hipStream_t s);
 hipError_t gemm_lmhead(const f16 *A, const void *W, bool w_f16, int rows, int vocab, int K,

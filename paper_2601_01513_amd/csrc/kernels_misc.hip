@@ -357,40 +357,73 @@ hipError_t launch_last_inputs(const float *x, const Branches &br, const TW *g, i
 }
 
 // ----------------------------------------------------- LSE merge and gather
-// Log-sum-exp of LM-head row t (T rows) over its vocabulary chunks, by one
-// wave (fixed order).
-__device__ __forceinline__ float wave_lse(const float2 *part, int nchunks, int T, int t) {
-  const int lane = threadIdx.x & 63;
-  float mx = -INFINITY;
-  for (int c = lane; c < nchunks; c += 64) mx = fmaxf(mx, part[(long)c * T + t].x);
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int c = lane; c < nchunks; c += 64) {
-    const float2 p = part[(long)c * T + t];
-    sum += p.y * __expf(p.x - mx);
+// Log-sum-exp of up to 16 LM-head rows (of T) over their vocabulary chunks, by
+// a block of NT threads: thread i takes row i % 16 (`t`, -1: none) and every
+// NT / 16th chunk, so a load covers the adjacent rows' partials of 4 chunks (a
+// wave per row read 64 lines per load and one 8-byte value of each); eight
+// loads in flight, rescaled to the thread's running maximum, then a tree over
+// the NT / 16 threads of a row. Returns the row's value to thread i < 16.
+template <int NT>
+__device__ __forceinline__ float block_lse(const float2 *part, int nchunks, int T, int t,
+                                           float2 *red) {
+  constexpr int U = 8, G = NT / 16;
+  const int tid = threadIdx.x;
+  float mx = -INFINITY, sum = 0.f;
+  if (t >= 0) {
+    for (int c0 = tid >> 4; c0 < nchunks; c0 += G * U) {
+      float2 p[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        p[u] = c0 + G * u < nchunks ? part[(long)(c0 + G * u) * T + t]
+                                    : make_float2(-INFINITY, 0.f);
+      float m = mx;
+#pragma unroll
+      for (int u = 0; u < U; ++u) m = fmaxf(m, p[u].x);
+      if (mx != m) sum = sum == 0.f ? 0.f : sum * __expf(mx - m);
+      mx = m;
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += p[u].y == 0.f ? 0.f : p[u].y * __expf(p[u].x - m);
+    }
   }
-  return mx + __logf(wave_sum(sum));
+  __syncthreads();  // an earlier call's values are used
+  red[tid] = make_float2(mx, sum);
+  __syncthreads();
+#pragma unroll
+  for (int o = NT / 2; o >= 16; o >>= 1) {
+    if (tid < o) {
+      const float2 x = red[tid], y = red[tid + o];
+      const float m = fmaxf(x.x, y.x);
+      red[tid] = make_float2(m, (x.y == 0.f ? 0.f : x.y * __expf(x.x - m)) +
+                                    (y.y == 0.f ? 0.f : y.y * __expf(y.x - m)));
+    }
+    __syncthreads();
+  }
+  return tid < 16 ? red[tid].x + __logf(red[tid].y) : 0.f;
 }
 
-// One block: wave w handles branches w, w+4, ...; then thread 0 takes the
-// maximum reliability and every thread marks its branches (Eq. 13).
-__global__ __launch_bounds__(256) void k_reliability_finish(int M, const float2 *part,
+// One block: the 2M rows (a branch's Yes row m, its No row M + m) 16 at a
+// time; then thread 0 takes the maximum reliability and every thread marks its
+// branches (Eq. 13).
+constexpr int RF_T = 1024;
+__global__ __launch_bounds__(RF_T) void k_reliability_finish(int M, const float2 *part,
                                                             int nchunks, const float *tgt,
                                                             float delta, float *lp_yes_no,
                                                             float *rel, int32_t *keep) {
-  __shared__ float r[kMaxCands];
+  __shared__ float lp[2 * kMaxCands], r[kMaxCands];
   __shared__ float best;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int m = w; m < M; m += 4) {
-    const float ly = tgt[m] - wave_lse(part, nchunks, 2 * M, m);
-    const float ln = tgt[M + m] - wave_lse(part, nchunks, 2 * M, M + m);
-    if (lane == 0) {
-      const float v = 1.f / (1.f + expf(ln - ly));
-      lp_yes_no[2 * m] = ly;
-      lp_yes_no[2 * m + 1] = ln;
-      rel[m] = v;
-      r[m] = v;
-    }
+  __shared__ float2 red[RF_T];
+  for (int i0 = 0; i0 < 2 * M; i0 += 16) {
+    const int i = i0 + (threadIdx.x & 15);
+    const float lse = block_lse<RF_T>(part, nchunks, 2 * M, i < 2 * M ? i : -1, red);
+    if (threadIdx.x < 16 && i < 2 * M) lp[i] = tgt[i] - lse;
+  }
+  __syncthreads();
+  for (int m = threadIdx.x; m < M; m += RF_T) {
+    const float ly = lp[m], ln = lp[M + m], v = 1.f / (1.f + expf(ln - ly));
+    lp_yes_no[2 * m] = ly;
+    lp_yes_no[2 * m + 1] = ln;
+    rel[m] = v;
+    r[m] = v;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -399,13 +432,13 @@ __global__ __launch_bounds__(256) void k_reliability_finish(int M, const float2 
     best = b;
   }
   __syncthreads();
-  for (int m = threadIdx.x; m < M; m += 256) keep[m] = r[m] >= best - delta ? 1 : 0;
+  for (int m = threadIdx.x; m < M; m += RF_T) keep[m] = r[m] >= best - delta ? 1 : 0;
 }
 
 hipError_t launch_reliability_finish(int M, const float2 *part, int nchunks,
                                      const float *tgt_logit, float delta, float *lp_yes_no,
                                      float *rel, int32_t *keep, hipStream_t s) {
-  k_reliability_finish<<<1, 256, 0, s>>>(M, part, nchunks, tgt_logit, delta, lp_yes_no, rel,
+  k_reliability_finish<<<1, RF_T, 0, s>>>(M, part, nchunks, tgt_logit, delta, lp_yes_no, rel,
                                          keep);
   return hipGetLastError();
 }
@@ -683,28 +716,26 @@ hipError_t launch_align_select(const float *ent, const float *frames, int M, int
   return hipGetLastError();
 }
 
-// One wave per output slot (m, j); lanes stride over the vocabulary chunks.
+// Block per 16 output slots (m, j).
 __global__ __launch_bounds__(256) void k_lse_gather(Branches br, const float2 *part,
                                                     int nchunks, const float *tgt_logit,
                                                     float *logprobs) {
-  const int slot = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (slot >= br.M * br.cmax) return;
-  const int m = slot / br.cmax, j = slot % br.cmax;
-  const int n = br.cu[m + 1] - br.cu[m];
-  if (j >= n) {
-    if (lane == 0) logprobs[slot] = 0.f;
-    return;
+  __shared__ float2 red[256];
+  const int slot = blockIdx.x * 16 + (threadIdx.x & 15);
+  const bool in = slot < br.M * br.cmax;
+  int t = -1;
+  if (in) {
+    const int m = slot / br.cmax, j = slot % br.cmax;
+    if (j < br.cu[m + 1] - br.cu[m]) t = br.cu[m] + j;
   }
-  const int t = br.cu[m] + j;
-  const float lse = wave_lse(part, nchunks, br.cu[br.M], t);
-  if (lane == 0) logprobs[slot] = tgt_logit[t] - lse;
+  const float lse = block_lse<256>(part, nchunks, br.cu[br.M], t, red);
+  if (threadIdx.x < 16 && in) logprobs[slot] = t < 0 ? 0.f : tgt_logit[t] - lse;
 }
 
 hipError_t launch_lse_gather(const Branches &br, const float2 *part, int nchunks,
                              const float *tgt_logit, float *logprobs, hipStream_t s) {
   const int slots = br.M * br.cmax;
-  k_lse_gather<<<(slots + 3) / 4, 256, 0, s>>>(br, part, nchunks, tgt_logit, logprobs);
+  k_lse_gather<<<(slots + 15) / 16, 256, 0, s>>>(br, part, nchunks, tgt_logit, logprobs);
   return hipGetLastError();
 }
 

@@ -65,40 +65,53 @@ __device__ __forceinline__ float sum_slices(const float *part, int ksplit, long 
 }
 
 // RG row groups of 16 activation rows; AS = 2: rows are [hi | lo] of width 2K.
-// ARGMAX (one K slice): instead of the products, each block writes, per row,
-// the largest of its 64 outputs and the lowest index holding it,
-// part[blockIdx.x][row] = (value, index bits).
-template <int RG, int AS, bool WCVT, bool ARGMAX>
+// NW groups of 16 weight rows per wave: two halve the activation loads per
+// weight byte but cost occupancy. SK_LSE takes two (16 rows of the 7B head in
+// bf16: 267 us against 288), the greedy head of a few drafts one (3 rows of
+// the 3B drafter's: 114 us against 125).
+// SK_ARGMAX and SK_LSE (LM head, one K slice): instead of the products, each
+// block writes, per row, over its 64 NW outputs, part[blockIdx.x][row] = (largest
+// value, its lowest index as bits) or (largest value m, sum of exp(l - m));
+// SK_LSE also writes the row's target logit if it is among them.
+enum { SK_PART, SK_ARGMAX, SK_LSE };
+template <int RG, int AS, bool WCVT, int OUT, int NW = 1>
 __global__ __launch_bounds__(256) void k_skinny(const f16 *__restrict__ A, int rows,
                                                 const uint16_t *__restrict__ W, int N, int K,
-                                                int ksplit, float *__restrict__ part) {
+                                                int ksplit, float *__restrict__ part,
+                                                const int32_t *__restrict__ tgt,
+                                                float *__restrict__ tgt_logit) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int b = blockIdx.x, s = blockIdx.y;
-  const int n0 = SK_ROWS * b + 16 * w;
+  const int n0 = SK_ROWS * NW * b + 16 * NW * w;
   // Slices are whole 256-wide steps (only the last one may end short).
   const int nsteps = (K + SK_STEP - 1) / SK_STEP;
   const int k0 = (int)((long)nsteps * s / ksplit) * SK_STEP;
   const int k1 = min(K, (int)((long)nsteps * (s + 1) / ksplit) * SK_STEP);
   const int sub = 8 * (lane >> 4);  // this lane's 8 of each 32-wide K piece
-  const uint16_t *wp = W + (long)(n0 + (lane & 15)) * K + sub;
+  const uint16_t *wp[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) wp[j] = W + (long)(n0 + 16 * j + (lane & 15)) * K + sub;
   const f16 *ap[RG];
 #pragma unroll
   for (int g = 0; g < RG; ++g)
     ap[g] = A + (long)min(g * 16 + (lane & 15), rows - 1) * K * AS + sub;
-  f32x4 acc[RG];
+  f32x4 acc[NW][RG];
 #pragma unroll
-  for (int g = 0; g < RG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < NW; ++j)
+#pragma unroll
+    for (int g = 0; g < RG; ++g) acc[j][g] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int k = k0; k < k1; k += SK_STEP) {
     // Every load of the step is issued before the first product; pieces past
     // the slice end (a short last step) re-load its last piece and multiply
     // zero activations (cnt is the same for the whole wave).
     const int cnt = min(SK_U, (k1 - k) / 32);
-    u32x4 wv[SK_U], av[SK_U][RG][AS];
+    u32x4 wv[SK_U][NW], av[SK_U][RG][AS];
 #pragma unroll
     for (int u = 0; u < SK_U; ++u) {
       const int kk = k + 32 * min(u, cnt - 1);
-      wv[u] = ld16(wp + kk);
+#pragma unroll
+      for (int j = 0; j < NW; ++j) wv[u][j] = ld16(wp[j] + kk);
 #pragma unroll
       for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -107,30 +120,33 @@ __global__ __launch_bounds__(256) void k_skinny(const f16 *__restrict__ A, int r
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < SK_U; ++u) {
-      const f16x8 wf = as_h8(WCVT ? sk_bf16_to_f16(wv[u]) : wv[u]);
       const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int g = 0; g < RG; ++g)
+      for (int j = 0; j < NW; ++j) {
+        const f16x8 wf = as_h8(WCVT ? sk_bf16_to_f16(wv[u][j]) : wv[u][j]);
 #pragma unroll
-        for (int h = 0; h < AS; ++h)
-          acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-              wf, as_h8(u < cnt ? av[u][g][h] : zero), acc[g], 0, 0, 0);
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+          for (int h = 0; h < AS; ++h)
+            acc[j][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                wf, as_h8(u < cnt ? av[u][g][h] : zero), acc[j][g], 0, 0, 0);
+      }
     }
   }
   // Lane l holds activation row l % 16 of each group and weight rows
-  // n0 + 4 (l / 16) + i, i < 4.
-  if constexpr (ARGMAX) {
+  // n0 + 16 j + 4 (l / 16) + i, i < 4.
+  if constexpr (OUT == SK_ARGMAX) {
     __shared__ float bv[4][16 * RG];
     __shared__ int bi[4][16 * RG];
 #pragma unroll
     for (int g = 0; g < RG; ++g) {
-      float v = acc[g][0];
+      float v = acc[0][g][0];
       int vi = n0 + 4 * (lane >> 4);
 #pragma unroll
-      for (int i = 1; i < 4; ++i)
-        if (acc[g][i] > v) {  // ascending indices: a strict > keeps the lowest
-          v = acc[g][i];
-          vi = n0 + 4 * (lane >> 4) + i;
+      for (int i = 1; i < 4 * NW; ++i)
+        if (acc[i >> 2][g][i & 3] > v) {  // ascending indices: a strict > keeps the lowest
+          v = acc[i >> 2][g][i & 3];
+          vi = n0 + 16 * (i >> 2) + 4 * (lane >> 4) + (i & 3);
         }
 #pragma unroll
       for (int o = 16; o < 64; o <<= 1) {
@@ -159,13 +175,48 @@ __global__ __launch_bounds__(256) void k_skinny(const f16 *__restrict__ A, int r
         }
       reinterpret_cast<float2 *>(part)[(long)b * rows + r] = make_float2(v, __int_as_float(vi));
     }
+  } else if constexpr (OUT == SK_LSE) {
+    __shared__ float2 red[4][16 * RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
+      const int r = g * 16 + (lane & 15);
+      const int at = r < rows ? tgt[r] - (n0 + 4 * (lane >> 4)) : -1;
+      float m = -INFINITY, sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4 * NW; ++i) {
+        if (at == 16 * (i >> 2) + (i & 3)) tgt_logit[r] = acc[i >> 2][g][i & 3];
+        m = fmaxf(m, acc[i >> 2][g][i & 3]);
+      }
+      m = fmaxf(m, __shfl_xor(m, 16, 64));
+      m = fmaxf(m, __shfl_xor(m, 32, 64));
+#pragma unroll
+      for (int i = 0; i < 4 * NW; ++i) {
+        const float x = acc[i >> 2][g][i & 3];
+        sum += x == -INFINITY ? 0.f : __expf(x - m);
+      }
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      if (lane < 16) red[w][g * 16 + lane] = make_float2(m, sum);
+    }
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r < 16 * RG && r < rows) {
+      float m = red[0][r].x;
+#pragma unroll
+      for (int i = 1; i < 4; ++i) m = fmaxf(m, red[i][r].x);
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        sum += red[i][r].y == 0.f ? 0.f : red[i][r].y * __expf(red[i][r].x - m);
+      reinterpret_cast<float2 *>(part)[(long)b * rows + r] = make_float2(m, sum);
+    }
   } else {
 #pragma unroll
     for (int g = 0; g < RG; ++g) {
       const int r = g * 16 + (lane & 15);
       if (r < rows)
         *reinterpret_cast<f32x4 *>(part + ((long)s * rows + r) * N + n0 + 4 * (lane >> 4)) =
-            acc[g];
+            acc[0][g];
     }
   }
 }
@@ -238,26 +289,45 @@ __global__ __launch_bounds__(256) void k_skinny_qkv(const float *__restrict__ pa
   qkv_store(o, n_heads, n_kv, slot, r, d, x1, x2);
 }
 
-template <bool ARGMAX, int RG, int AS>
+template <int OUT, int RG, int AS, int NW = 1>
 hipError_t launch_rg(const f16 *A, int rows, const void *W, bool w_f16, int N, int K, int ks,
-                     float *part, hipStream_t s) {
-  const dim3 grid(N / SK_ROWS, ks);
+                     float *part, hipStream_t s, const int32_t *tgt, float *tgt_logit) {
+  const dim3 grid(N / (SK_ROWS * NW), ks);
   const uint16_t *W16 = static_cast<const uint16_t *>(W);
   if (w_f16)
-    k_skinny<RG, AS, false, ARGMAX><<<grid, 256, 0, s>>>(A, rows, W16, N, K, ks, part);
+    k_skinny<RG, AS, false, OUT, NW><<<grid, 256, 0, s>>>(A, rows, W16, N, K, ks, part, tgt,
+                                                      tgt_logit);
   else
-    k_skinny<RG, AS, true, ARGMAX><<<grid, 256, 0, s>>>(A, rows, W16, N, K, ks, part);
+    k_skinny<RG, AS, true, OUT, NW><<<grid, 256, 0, s>>>(A, rows, W16, N, K, ks, part, tgt,
+                                                     tgt_logit);
   return hipGetLastError();
 }
 
-template <bool ARGMAX = false>
 hipError_t launch(const f16 *A, int rows, int asplit, const void *W, bool w_f16, int N, int K,
                   int ks, float *part, hipStream_t s) {
   if (rows <= 16)
-    return asplit == 2 ? launch_rg<ARGMAX, 1, 2>(A, rows, W, w_f16, N, K, ks, part, s)
-                       : launch_rg<ARGMAX, 1, 1>(A, rows, W, w_f16, N, K, ks, part, s);
-  return asplit == 2 ? launch_rg<ARGMAX, 2, 2>(A, rows, W, w_f16, N, K, ks, part, s)
-                     : launch_rg<ARGMAX, 2, 1>(A, rows, W, w_f16, N, K, ks, part, s);
+    return asplit == 2
+               ? launch_rg<SK_PART, 1, 2>(A, rows, W, w_f16, N, K, ks, part, s, nullptr, nullptr)
+               : launch_rg<SK_PART, 1, 1>(A, rows, W, w_f16, N, K, ks, part, s, nullptr, nullptr);
+  return asplit == 2
+             ? launch_rg<SK_PART, 2, 2>(A, rows, W, w_f16, N, K, ks, part, s, nullptr, nullptr)
+             : launch_rg<SK_PART, 2, 1>(A, rows, W, w_f16, N, K, ks, part, s, nullptr, nullptr);
+}
+
+// LM head of few rows (unsplit activations, one K slice).
+template <int OUT>
+hipError_t launch_lm(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
+                     float2 *part, hipStream_t s, const int32_t *tgt, float *tgt_logit) {
+  if (rows < 1 || rows > kSkinnyMaxRows || vocab % SK_ROWS || K % 32 || K <= 0)
+    return hipErrorInvalidValue;
+  float *p = reinterpret_cast<float *>(part);
+  constexpr int NW = OUT == SK_LSE ? 2 : 1;
+  if (vocab % (SK_ROWS * NW) == 0)
+    return rows <= 16
+               ? launch_rg<OUT, 1, 1, NW>(A, rows, W, w_f16, vocab, K, 1, p, s, tgt, tgt_logit)
+               : launch_rg<OUT, 2, 1, NW>(A, rows, W, w_f16, vocab, K, 1, p, s, tgt, tgt_logit);
+  return rows <= 16 ? launch_rg<OUT, 1, 1>(A, rows, W, w_f16, vocab, K, 1, p, s, tgt, tgt_logit)
+                    : launch_rg<OUT, 2, 1>(A, rows, W, w_f16, vocab, K, 1, p, s, tgt, tgt_logit);
 }
 
 bool skinny_args_ok(int rows, int N, int K, int asplit) {
@@ -317,12 +387,20 @@ hipError_t skinny_qkv_rope(const f16 *A, int rows, int asplit, const void *W, bo
 
 int skinny_lm_chunks(int vocab) { return vocab % SK_ROWS ? 0 : vocab / SK_ROWS; }
 
+int skinny_lse_chunks(int vocab) {
+  return vocab % (2 * SK_ROWS) == 0 ? vocab / (2 * SK_ROWS) : skinny_lm_chunks(vocab);
+}
+
 hipError_t skinny_lmargmax(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
                            float2 *part, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  if (rows < 1 || rows > kSkinnyMaxRows || vocab % SK_ROWS || K % 32 || K <= 0)
-    return hipErrorInvalidValue;
-  return launch<true>(A, rows, 1, W, w_f16, vocab, K, 1, reinterpret_cast<float *>(part), s);
+  return launch_lm<SK_ARGMAX>(A, rows, W, w_f16, vocab, K, part, s, nullptr, nullptr);
+}
+
+hipError_t skinny_lmhead(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
+                         const int32_t *lm_tgt, float2 *part, float *tgt_logit, hipStream_t s) {
+  if (rows == 0) return hipSuccess;
+  return launch_lm<SK_LSE>(A, rows, W, w_f16, vocab, K, part, s, lm_tgt, tgt_logit);
 }
 
 }  // namespace vsr

@@ -178,11 +178,11 @@ Plan make_plan(const vsr_config &c) {
   p.vtd_lo = take(nprec * dec_cache);
   p.part_acc = take(part_rows * c.n_kv_heads * hd * 4);
   p.part_ml = take(part_rows * c.n_kv_heads * 8);
-  // LM-head partials: vocabulary tiles x rows, or (greedy drafts of few
-  // branches) 64-entry chunks x branches.
+  // LM-head partials: vocabulary tiles x rows, or (few rows) 64-entry chunks
+  // x rows.
   p.lm_part = take(std::max((size_t)p.lm_chunks * p.lm_rows,
                             c.dtype == VSR_BF16 ? (size_t)skinny_lm_chunks(c.vocab) *
-                                                      std::min(c.max_cands, kSkinnyMaxRows)
+                                                      std::min(p.lm_rows, kSkinnyMaxRows)
                                                 : 0) *
                    8);
   p.tgt = take((size_t)p.lm_rows * 4);
@@ -661,11 +661,22 @@ int lm_head(vsr_ctx *c, int rows, int *chunks) {
   float2 *lm_part = c->at<float2>(p.lm_part);
   float *tgt = c->at<float>(p.tgt);
   *chunks = p.lm_chunks;
-  if constexpr (kMfma)
-    STAGE(c, K_LMHEAD, "lm head",
-          gemm_lmhead(lm_in, c->lm_head, cf.gemm_weights == VSR_F16, rows, cf.vocab,
-                      cf.d_model, lm_tgt, lm_part, tgt, s));
-  else
+  const bool wf16 = cf.gemm_weights == VSR_F16;
+  // Few rows (a reliability call has two per branch): the head is a stream
+  // over the weights; a 256-row tile spends its matrix work on padding. 16
+  // rows of the 7B head kept in bf16 (1.09 GB): 390 -> 267 us.
+  if constexpr (kMfma) {
+    if (rows <= kSkinnyMaxRows && skinny_lse_chunks(cf.vocab) > 0) {
+      *chunks = skinny_lse_chunks(cf.vocab);
+      STAGE(c, K_LMHEAD, "lm head",
+            skinny_lmhead(lm_in, rows, c->lm_head, wf16, cf.vocab, cf.d_model, lm_tgt, lm_part,
+                          tgt, s));
+    } else {
+      STAGE(c, K_LMHEAD, "lm head",
+            gemm_lmhead(lm_in, c->lm_head, wf16, rows, cf.vocab, cf.d_model, lm_tgt, lm_part,
+                        tgt, s));
+    }
+  } else
     STAGE(c, K_LMHEAD, "lm head",
           f32_lmhead(lm_in, nullptr, 0.f, nullptr, nullptr, static_cast<const TW *>(c->lm_head),
                      rows, cf.vocab, cf.d_model, lm_tgt, lm_part, tgt, s));

@@ -1,0 +1,44 @@
+"""The LM head of few rows (up to 32: a stream over the weights) beside the
+tiled one: both sides of the line, one and two row groups, the three chunk
+forms of the vocabulary (multiples of 128, of 64, neither), and both weight
+storages, which must agree bit for bit. Bar: 2e-2 per token, the bar of the
+fp16-operand path."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_01513_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [1152, 1088, 1000])
+@pytest.mark.parametrize("lens", [[1, 0], [9, 7], [16, 1], [16, 16], [16, 17]])
+def test_lm_head_of_few_rows(vocab, lens):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = W.VerifierConfig(
+        name=f"few rows V{vocab} {lens}", n_layers=1, d_model=256, n_heads=2, n_kv_heads=1,
+        head_dim=128, d_ff=128, vocab=vocab, rope_base=1e6, dtype=W.BF16, n_prefix=40,
+        n_visual=8, n_cands=2, cand_len=17)
+    wl = W.make_workload(cfg, sum(lens), device="cuda")
+    wl.cand_ids[0, 0] = vocab - 1  # a target in the last chunk
+    for m in range(2):
+        wl.cand_ids[m, lens[m]:] = 0
+    lens = np.asarray(lens, dtype=np.int32)
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    out = []
+    for storage in ("f16", "bf16"):
+        v = Verifier(cfg, wl.weights, device="cuda", gemm_weights=storage)
+        v.prefill(wl.visual, ids)
+        out.append([t.cpu().numpy() for t in v.score(cids, lens)])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    ref, sc, am = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights),
+                                             W.to_host_f32(wl.visual), wl.prefix_ids,
+                                             wl.cand_ids, lens)
+    assert np.abs(out[0][0] - ref).max() <= 2e-2
+    assert int(out[0][2][0]) == am or abs(sc[0] - sc[1]) < 0.1
