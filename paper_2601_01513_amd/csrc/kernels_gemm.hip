@@ -559,7 +559,10 @@ __global__ __launch_bounds__(NT) void k_gemm_swiglu(const f16 *__restrict__ A,
 // 5.8% to 2.4% of the loop, gate/up 2% faster). fp16 operands only, K a
 // multiple of 64, and every byte offset into A and B below 4 GiB (the loads
 // take 32-bit offsets from 64-bit bases).
-template <class ARow, class BRow>
+// AS = 2: A rows are [hi | lo] (2 K wide) and B is walked twice, as in the
+// 8-wave loop: the block runs once per half of the panels [kt0, kt1) of 2 K,
+// the accumulators staying in place, in the same order of products.
+template <int AS, class ARow, class BRow>
 __device__ __forceinline__ void mainloop_4w(const void *A, ARow arow, const void *B, BRow brow,
                                             int K, int kt0, int kt1, u32x4 *lds,
                                             f32x16 (&acc)[4][4]) {
@@ -569,21 +572,9 @@ __device__ __forceinline__ void mainloop_4w(const void *A, ARow arow, const void
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-  const int n = kt1 - kt0;
-  if (n <= 0) return;
+  if (kt1 <= kt0) return;
   // The LDS byte address is the low half of the array's generic address.
   const uint32_t lb = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  // LDS-direct load i of wave w fills tile rows (4 i + w) * 8 .. + 7; lane l
-  // lands in physical chunk l % 8 of row l / 8 (so the four waves' load i
-  // fill rows 32 i .. + 31, the rows of fragment i).
-  uint32_t dA[8], dB[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = (i * 4 + w) * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((row >> 1) & 7);
-    dA[i] = static_cast<uint32_t>(((size_t)arow(row) * K + c * 8) * 2 + (size_t)kt0 * 128);
-    dB[i] = static_cast<uint32_t>(((size_t)brow(row) * K + c * 8) * 2 + (size_t)kt0 * 128);
-  }
   // Fragment reads of k-step s: row (lane % 32) of the wave's first 32-row
   // block, chunk 2 s + lane / 32, swizzled; blocks 1..3 and the other
   // stages are immediate offsets (4 KB per block, 32 KB per stage), except
@@ -598,35 +589,53 @@ __device__ __forceinline__ void mainloop_4w(const void *A, ARow arow, const void
     rdC[s] = rdB[s] + 65536;
   }
   const uint32_t mw = __builtin_amdgcn_readfirstlane(lb + w * 1024);
-  int np = __builtin_amdgcn_readfirstlane(n);
-  u32x4 fa00, fa01, fa02, fa03, fb00, fb01, fb02, fb03;
-  u32x4 fa10, fa11, fa12, fa13, fb10, fb11, fb12, fb13;
-  // M0 is a reserved register, so its clobber draws a note that the
-  // compiler may not preserve it: nothing in these kernels keeps a value in
-  // M0 across the block (the loads set it before each use).
+  const int nkb = K / BK;
+  for (int kt = kt0; kt < kt1;) {
+    const int end = AS == 2 && kt < nkb ? min(kt1, nkb) : kt1, ktb = kt < nkb ? kt : kt - nkb;
+    // LDS-direct load i of wave w fills tile rows (4 i + w) * 8 .. + 7; lane l
+    // lands in physical chunk l % 8 of row l / 8 (so the four waves' load i
+    // fill rows 32 i .. + 31, the rows of fragment i).
+    uint32_t dA[8], dB[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = (i * 4 + w) * 8 + (lane >> 3);
+      const int c = (lane & 7) ^ ((row >> 1) & 7);
+      dA[i] = static_cast<uint32_t>(((size_t)arow(row) * K * AS + c * 8) * 2 + (size_t)kt * 128);
+      dB[i] = static_cast<uint32_t>(((size_t)brow(row) * K + c * 8) * 2 + (size_t)ktb * 128);
+    }
+    int np = __builtin_amdgcn_readfirstlane(end - kt);
+    u32x4 fa00, fa01, fa02, fa03, fb00, fb01, fb02, fb03;
+    u32x4 fa10, fa11, fa12, fa13, fb10, fb11, fb12, fb13;
+    // M0 is a reserved register, so its clobber draws a note that the
+    // compiler may not preserve it: nothing in these kernels keeps a value in
+    // M0 across the block (the loads set it before each use).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-  asm volatile(
+    asm volatile(
 #include "gemm_loop_4w.inc"
-      : [c00] "+a"(acc[0][0]), [c01] "+a"(acc[0][1]), [c02] "+a"(acc[0][2]), [c03] "+a"(acc[0][3]),
-        [c10] "+a"(acc[1][0]), [c11] "+a"(acc[1][1]), [c12] "+a"(acc[1][2]), [c13] "+a"(acc[1][3]),
-        [c20] "+a"(acc[2][0]), [c21] "+a"(acc[2][1]), [c22] "+a"(acc[2][2]), [c23] "+a"(acc[2][3]),
-        [c30] "+a"(acc[3][0]), [c31] "+a"(acc[3][1]), [c32] "+a"(acc[3][2]), [c33] "+a"(acc[3][3]),
-        [fa00] "=&v"(fa00), [fa01] "=&v"(fa01), [fa02] "=&v"(fa02), [fa03] "=&v"(fa03),
-        [fb00] "=&v"(fb00), [fb01] "=&v"(fb01), [fb02] "=&v"(fb02), [fb03] "=&v"(fb03),
-        [fa10] "=&v"(fa10), [fa11] "=&v"(fa11), [fa12] "=&v"(fa12), [fa13] "=&v"(fa13),
-        [fb10] "=&v"(fb10), [fb11] "=&v"(fb11), [fb12] "=&v"(fb12), [fb13] "=&v"(fb13),
-        [dA0] "+v"(dA[0]), [dA1] "+v"(dA[1]), [dA2] "+v"(dA[2]), [dA3] "+v"(dA[3]),
-        [dA4] "+v"(dA[4]), [dA5] "+v"(dA[5]), [dA6] "+v"(dA[6]), [dA7] "+v"(dA[7]),
-        [dB0] "+v"(dB[0]), [dB1] "+v"(dB[1]), [dB2] "+v"(dB[2]), [dB3] "+v"(dB[3]),
-        [dB4] "+v"(dB[4]), [dB5] "+v"(dB[5]), [dB6] "+v"(dB[6]), [dB7] "+v"(dB[7]),
-        [n] "+s"(np)
-      : [rdA0] "v"(rdA[0]), [rdA1] "v"(rdA[1]), [rdA2] "v"(rdA[2]), [rdA3] "v"(rdA[3]),
-        [rdB0] "v"(rdB[0]), [rdB1] "v"(rdB[1]), [rdB2] "v"(rdB[2]), [rdB3] "v"(rdB[3]),
-        [rdC0] "v"(rdC[0]), [rdC1] "v"(rdC[1]), [rdC2] "v"(rdC[2]), [rdC3] "v"(rdC[3]),
-        [pa] "s"(A), [pb] "s"(B), [mw] "s"(mw)
-      : "memory", "m0", "scc");
+        : [c00] "+a"(acc[0][0]), [c01] "+a"(acc[0][1]), [c02] "+a"(acc[0][2]), [c03] "+a"(acc[0][3]),
+          [c10] "+a"(acc[1][0]), [c11] "+a"(acc[1][1]), [c12] "+a"(acc[1][2]), [c13] "+a"(acc[1][3]),
+          [c20] "+a"(acc[2][0]), [c21] "+a"(acc[2][1]), [c22] "+a"(acc[2][2]), [c23] "+a"(acc[2][3]),
+          [c30] "+a"(acc[3][0]), [c31] "+a"(acc[3][1]), [c32] "+a"(acc[3][2]), [c33] "+a"(acc[3][3]),
+          [fa00] "=&v"(fa00), [fa01] "=&v"(fa01), [fa02] "=&v"(fa02), [fa03] "=&v"(fa03),
+          [fb00] "=&v"(fb00), [fb01] "=&v"(fb01), [fb02] "=&v"(fb02), [fb03] "=&v"(fb03),
+          [fa10] "=&v"(fa10), [fa11] "=&v"(fa11), [fa12] "=&v"(fa12), [fa13] "=&v"(fa13),
+          [fb10] "=&v"(fb10), [fb11] "=&v"(fb11), [fb12] "=&v"(fb12), [fb13] "=&v"(fb13),
+          [dA0] "+v"(dA[0]), [dA1] "+v"(dA[1]), [dA2] "+v"(dA[2]), [dA3] "+v"(dA[3]),
+          [dA4] "+v"(dA[4]), [dA5] "+v"(dA[5]), [dA6] "+v"(dA[6]), [dA7] "+v"(dA[7]),
+          [dB0] "+v"(dB[0]), [dB1] "+v"(dB[1]), [dB2] "+v"(dB[2]), [dB3] "+v"(dB[3]),
+          [dB4] "+v"(dB[4]), [dB5] "+v"(dB[5]), [dB6] "+v"(dB[6]), [dB7] "+v"(dB[7]),
+          [n] "+s"(np)
+        : [rdA0] "v"(rdA[0]), [rdA1] "v"(rdA[1]), [rdA2] "v"(rdA[2]), [rdA3] "v"(rdA[3]),
+          [rdB0] "v"(rdB[0]), [rdB1] "v"(rdB[1]), [rdB2] "v"(rdB[2]), [rdB3] "v"(rdB[3]),
+          [rdC0] "v"(rdC[0]), [rdC1] "v"(rdC[1]), [rdC2] "v"(rdC[2]), [rdC3] "v"(rdC[3]),
+          [pa] "s"(A), [pb] "s"(B), [mw] "s"(mw)
+        : "memory", "m0", "scc");
 #pragma clang diagnostic pop
+    kt = end;
+    if (AS == 1) break;
+    if (kt < kt1) __syncthreads();  // every wave is past its last LDS reads
+  }
 }
 
 // Tile row of accumulator register r of block row i (four-wave tile).
@@ -649,10 +658,11 @@ __device__ __forceinline__ void store_partial_4w(const f32x16 (&acc)[4][4], floa
   }
 }
 
-// x += A . W^T on the four-wave tile (fp16 weights, unsplit activations).
+// x += A . W^T on the four-wave tile (fp16 weights).
 // The residual values of two block rows (32 per lane) are loaded before any
 // of them is stored back: the compiler cannot move a load of x above a
 // store to x, and 64 at a time spilled registers.
+template <int AS>
 __global__ __launch_bounds__(256) void k_gemm_residual_4w(const f16 *__restrict__ A,
                                                           const uint16_t *__restrict__ W,
                                                           int rows, int N, int K, Launch ln,
@@ -662,10 +672,10 @@ __global__ __launch_bounds__(256) void k_gemm_residual_4w(const f16 *__restrict_
   const Work wk = block_work(ln);
   const int m0 = wk.tm * 256, n0 = wk.tn * 256;
   const bool split = wk.tail >= 0;
-  int k0 = 0, k1 = K / BK;
+  int k0 = 0, k1 = K / BK * AS;
   if (split) split_range(k1, ln.nsplit, wk.split, k0, k1);
   f32x16 acc[4][4];
-  mainloop_4w(
+  mainloop_4w<AS>(
       A, [=](int r) { return min(m0 + r, rows - 1); }, W,
       [=](int r) { return min(n0 + r, N - 1); }, K, k0, k1, lds, acc);
   if (split) {
@@ -677,9 +687,9 @@ __global__ __launch_bounds__(256) void k_gemm_residual_4w(const f16 *__restrict_
                        x);
 }
 
-// Gate/up projection + SwiGLU on the four-wave tile (fp16 weights, unsplit
-// activations). A wave's 128 B rows are 64 gate + 64 up rows, as in the
+// Gate/up projection + SwiGLU on the four-wave tile (fp16 weights). A wave's 128 B rows are 64 gate + 64 up rows, as in the
 // 8-wave kernel, so block columns j and j + 2 pair up in one lane.
+template <int AS>
 __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ A,
                                                         const uint16_t *__restrict__ W, int rows,
                                                         int F, int K, Launch ln,
@@ -689,10 +699,10 @@ __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ 
   const Work wk = block_work(ln);
   const int m0 = wk.tm * 256, o0 = wk.tn * 128;
   const bool split = wk.tail >= 0;
-  int k0 = 0, k1 = K / BK;
+  int k0 = 0, k1 = K / BK * AS;
   if (split) split_range(k1, ln.nsplit, wk.split, k0, k1);
   f32x16 acc[4][4];
-  mainloop_4w(
+  mainloop_4w<AS>(
       A, [=](int r) { return min(m0 + r, rows - 1); }, W,
       [=](int r) {
         const int q = r & 127;
@@ -722,8 +732,13 @@ __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ 
               __builtin_amdgcn_update_dpp(0, __float_as_int(odd ? a : b), 0xB1, 0xF, 0xF, false));
           const float v0 = odd ? got : a, v1 = odd ? b : got;
           const int row = m0 + row_4w(wm, i, 2 * k + (odd ? 1 : 0), lane);
-          *reinterpret_cast<f16x2 *>(h + (long)row * F + c0) =
-              f16x2{static_cast<f16>(v0), static_cast<f16>(v1)};
+          const f16 h0 = static_cast<f16>(v0), h1 = static_cast<f16>(v1);
+          f16 *dst = h + (long)row * F * AS + c0;
+          *reinterpret_cast<f16x2 *>(dst) = f16x2{h0, h1};
+          if (AS == 2)
+            *reinterpret_cast<f16x2 *>(dst + F) =
+                f16x2{static_cast<f16>(v0 - static_cast<float>(h0)),
+                      static_cast<f16>(v1 - static_cast<float>(h1))};
         }
     }
     return;
@@ -737,7 +752,8 @@ __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ 
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = m0 + row_4w(wm, i, r, lane);
-        if (row < rows) h[(long)row * F + col] = static_cast<f16>(silu_mul(acc[i][j][r], acc[i][j + 2][r]));
+        if (row < rows)
+          store_act(h, (long)row * F * AS, col, F, AS, silu_mul(acc[i][j][r], acc[i][j + 2][r]));
       }
   }
 }
@@ -1146,7 +1162,7 @@ __global__ __launch_bounds__(256) void k_gemm_lmhead_4w(const f16 *__restrict__ 
   const Work wk = block_work(ln);
   const int m0 = wk.tm * 256, n0 = wk.tn * 256;
   f32x16 acc[4][4];
-  mainloop_4w(
+  mainloop_4w<1>(
       Wlm, [=](int r) { return min(m0 + r, vocab - 1); }, Hn,
       [=](int r) { return min(n0 + r, T - 1); }, K, 0, K / BK, lds, acc);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
@@ -1301,12 +1317,24 @@ constexpr int kFourWave = 3 | 8;
 #endif
 constexpr int kFourWaveMinK = 8192;
 
-// The four-wave kernels' conditions: fp16 weights, unsplit activations, and
-// 32-bit byte offsets reaching every operand row.
+// The four-wave kernels' conditions: fp16 weights, and 32-bit byte offsets
+// reaching every operand row. Split activations gain as plain ones do: the 32B
+// layer's split gate/up product (10240 rows) takes 4W_SWIGLU against 11.0 ms
+// on the 8-wave tile, its split down product 4W_DOWN.
 inline bool four_wave_ok(bool w_f16, int asplit, int rows, int nrows_w, int K) {
-  return w_f16 && asplit == 1 && K % BK == 0 && (size_t)rows * K * 2 <= UINT32_MAX &&
+  return w_f16 && K % BK == 0 && (size_t)rows * K * asplit * 2 <= UINT32_MAX &&
          (size_t)nrows_w * K * 2 <= UINT32_MAX;
 }
+
+// Launch of four-wave kernel `kern<AS>`.
+#define VSR_4W_LAUNCH(kern, ...)                                                   \
+  do {                                                                            \
+    const uint16_t *W16 = static_cast<const uint16_t *>(W);                       \
+    if (asplit == 2)                                                              \
+      kern<2><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                            \
+    else                                                                          \
+      kern<1><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                            \
+  } while (0)
 
 // Weight-format dispatch of a GEMM kernel launch.
 #define VSR_WLAUNCH(kern, grid, ...)                                              \
@@ -1327,10 +1355,9 @@ hipError_t gemm_residual(const f16 *A, const void *W, bool w_f16, int rows, int 
   if ((size_t)rows * N * 4 > INT32_MAX) return hipErrorInvalidValue;
   const Launch ln = plan_launch((rows + TL::BM - 1) / TL::BM, (N + TL::BN - 1) / TL::BN, 8,
                                 K / BK * asplit);
-  const int fw = K >= kFourWaveMinK ? 2 : 4;
+  const int fw = K * asplit >= kFourWaveMinK ? 2 : 4;
   if ((kFourWave & fw) && four_wave_ok(w_f16, asplit, rows, N, K))
-    k_gemm_residual_4w<<<ln.blocks(), 256, 0, s>>>(A, static_cast<const uint16_t *>(W), rows, N, K,
-                                                     ln, x, part);
+    VSR_4W_LAUNCH(k_gemm_residual_4w, A, W16, rows, N, K, ln, x, part);
   else
     VSR_WLAUNCH(k_gemm_residual, ln.blocks(), A, W16, rows, N, K, asplit, ln, x, part);
   if (ln.ntail > 0)
@@ -1351,8 +1378,7 @@ hipError_t gemm_swiglu(const f16 *A, const void *W, bool w_f16, int rows, int F,
   // The four-wave tile with the ordered K loop where it applies (same
   // tiles, same partial layout).
   if ((kFourWave & 1) && four_wave_ok(w_f16, asplit, rows, 2 * F, K))
-    k_gemm_swiglu_4w<<<ln.blocks(), 256, 0, s>>>(A, static_cast<const uint16_t *>(W), rows, F, K,
-                                                   ln, h, part);
+    VSR_4W_LAUNCH(k_gemm_swiglu_4w, A, W16, rows, F, K, ln, h, part);
   else
     VSR_WLAUNCH(k_gemm_swiglu, ln.blocks(), A, W16, rows, F, K, asplit, ln, h, part);
   if (ln.ntail > 0)
@@ -1387,7 +1413,12 @@ hipError_t gemm_lmhead(const f16 *A, const void *W, bool w_f16, int rows, int vo
   // partials).
   const int nm = lmhead_chunks(vocab), nn = (rows + TL::BN - 1) / TL::BN;
   const Launch ln{nm, nn, 1, nm * nn, 0, 1};
-  if ((kFourWave & 8) && four_wave_ok(w_f16, 1, vocab, rows, K))
+  // At most 128 tokens: half a token tile of padding costs more than the
+  // smaller tile's extra LDS reads (LM128).
+  if (rows <= 128) {
+    typedef Tile<256, 128, 4, 2> TL;
+    VSR_WLAUNCH(k_gemm_lmhead, ln.blocks(), A, W16, rows, vocab, K, ln, lm_tgt, part, tgt_logit);
+  } else if ((kFourWave & 8) && four_wave_ok(w_f16, 1, vocab, rows, K))
     k_gemm_lmhead_4w<<<ln.blocks(), 256, 0, s>>>(A, static_cast<const uint16_t *>(W), rows, vocab,
                                                    K, ln, lm_tgt, part, tgt_logit);
   else
@@ -1406,6 +1437,7 @@ hipError_t gemm_lmargmax(const f16 *A, const void *W, bool w_f16, int rows, int 
 }
 
 #undef VSR_WLAUNCH
+#undef VSR_4W_LAUNCH
 #undef VSR_REDUCE_LAUNCH
 
 namespace {

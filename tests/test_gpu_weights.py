@@ -7,6 +7,8 @@ import sys
 import numpy as np
 import pytest
 
+import oracle
+
 from paper_2601_01513_amd import workload as W
 
 pytestmark = pytest.mark.gpu
@@ -77,3 +79,31 @@ def test_fp16_and_bf16_weight_storage_score_identically(cfg):
     np.testing.assert_array_equal(res["bf16"][0], res["f16"][0])
     np.testing.assert_array_equal(res["bf16"][1], res["f16"][1])
     assert res["bf16"][2] == res["f16"][2]
+
+
+@pytest.mark.parametrize("rows,ff", [(3, 320), (300, 4160), (513, 4224), (700, 1216)])
+def test_split_products_agree_between_the_weight_forms(rows, ff):
+    """Precise layers with a split feed-forward block: fp16 weights run their
+    split products on the four-wave tile (gate/up at every size, the down
+    product from 2 K = 8192 on), bf16 weights on the eight-wave one; the same
+    products in the same order, so the log-probs are bit for bit equal. Whole
+    and partial tiles, split-K tails of both halves."""
+    torch = _torch()
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = W.VerifierConfig(
+        name=f"split rows {rows} F{ff}", n_layers=2, d_model=256, n_heads=2, n_kv_heads=1,
+        head_dim=128, d_ff=ff, vocab=500, rope_base=1e6, dtype=W.BF16, n_prefix=rows,
+        n_visual=0, n_cands=3, cand_len=50)
+    wl = W.make_workload(cfg, 1, device="cuda")
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    out = []
+    for storage in ("f16", "bf16"):
+        v = Verifier(cfg, wl.weights, device="cuda", gemm_weights=storage, split_layers=2,
+                     split_mlp_layers=2)
+        out.append(v.verify(None, ids, cids, [50, 17, 3])[0].cpu().numpy())
+    np.testing.assert_array_equal(out[0], out[1])
+    ref = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights), W.to_host_f32(wl.visual),
+                                     wl.prefix_ids, wl.cand_ids, [50, 17, 3])[0]
+    valid = np.arange(50)[None, :] < np.asarray([50, 17, 3])[:, None]
+    assert np.abs(out[0] - ref)[valid].max() <= 2e-2
