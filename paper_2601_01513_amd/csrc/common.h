@@ -227,12 +227,16 @@ __device__ __forceinline__ int qkv_row_pos(const QKVOut<f16> &o, int row) {
   return p ? *p : row;
 }
 
+// Cache position of row `row`'s key and value.
+__device__ __forceinline__ int qkv_cache_row(const QKVOut<f16> &o, int row) {
+  return row >= o.split ? row - o.split : o.cache_row ? o.cache_row[row] : row;
+}
+
 // qkv_store without the rotary: x1, x2 are the pair as stored (queries and
-// keys already rotated).
-__device__ __forceinline__ void qkv_store_rotated(const QKVOut<f16> &o, int n_heads, int n_kv,
-                                                  int slot, int row, int d, float x1, float x2) {
+// keys already rotated), crow the row's cache position.
+__device__ __forceinline__ void qkv_store_at(const QKVOut<f16> &o, int n_heads, int n_kv, int slot,
+                                             int row, int d, float x1, float x2, int crow) {
   const bool second = row >= o.split;  // a candidate row of a fused pass
-  const int row2 = row - o.split;
   const f16 h1 = static_cast<f16>(x1), h2 = static_cast<f16>(x2);
   const f16 l1 = static_cast<f16>(x1 - static_cast<float>(h1));
   const f16 l2 = static_cast<f16>(x2 - static_cast<float>(h2));
@@ -245,7 +249,6 @@ __device__ __forceinline__ void qkv_store_rotated(const QKVOut<f16> &o, int n_he
       o.q_lo[off + d + 64] = l2;
     }
   } else {
-    const int crow = second ? row2 : o.cache_row ? o.cache_row[row] : row;
     const int npos = second ? o.kv_npos2 : o.kv_npos;
     if (slot < n_heads + n_kv) {
       f16 *k = second ? o.k2 : o.k, *k_lo = second ? o.k2_lo : o.k_lo;
@@ -271,6 +274,12 @@ __device__ __forceinline__ void qkv_store_rotated(const QKVOut<f16> &o, int n_he
       }
     }
   }
+}
+
+__device__ __forceinline__ void qkv_store_rotated(const QKVOut<f16> &o, int n_heads, int n_kv,
+                                                  int slot, int row, int d, float x1, float x2) {
+  qkv_store_at(o, n_heads, n_kv, slot, row, d, x1, x2,
+               slot < n_heads ? 0 : qkv_cache_row(o, row));
 }
 
 // The rotate-half pair of query / key slots turned by the rotary-table entry
@@ -365,6 +374,17 @@ hipError_t skinny_qkv_rope(const f16 *A, int rows, int asplit, const void *W, bo
 int skinny_lm_chunks(int vocab);
 hipError_t skinny_lmargmax(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
                            float2 *part, hipStream_t s);
+// Projections of at most 8 rows as one launch each, the first two with the
+// RMSNorm (gain g) of the residual rows x; for the sizes few_ok takes (att =
+// n_heads * head_dim).
+bool few_ok(int rows, int d, int att, int F);
+hipError_t few_qkv_rope(const float *x, const bf16 *g, float eps, int rows, int asplit,
+                        const void *W, bool w_f16, int K, int n_heads, int n_kv,
+                        const QKVOut<f16> &out, hipStream_t s);
+hipError_t few_swiglu(const float *x, const bf16 *g, float eps, int rows, int asplit,
+                      const void *W, bool w_f16, int F, int K, f16 *h, hipStream_t s);
+hipError_t few_residual(const f16 *A, int rows, int asplit, const void *W, bool w_f16, int N,
+                        int K, float *x, hipStream_t s);
 // LM head of few rows as gemm_lmhead, in skinny_lse_chunks(vocab) equal chunks
 // (0: not supported).
 int skinny_lse_chunks(int vocab);

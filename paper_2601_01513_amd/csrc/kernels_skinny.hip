@@ -14,6 +14,9 @@
 // 64 weight rows and the same K slice, so their activation loads hit the same
 // cache lines.
 //
+// Up to 8 rows of the usual widths take k_few below, one launch per projection;
+// what follows is the form of up to 32 rows and any width.
+//
 // The K slices write fp32 partials part[s][row][n]; a small reduce kernel
 // sums them in slice order (deterministic) and applies the epilogue: residual
 // add (+ the RMSNorm that follows), SwiGLU, or rotary + cache scatter. (A
@@ -289,6 +292,246 @@ __global__ __launch_bounds__(256) void k_skinny_qkv(const float *__restrict__ pa
   qkv_store(o, n_heads, n_kv, slot, r, d, x1, x2);
 }
 
+// ------------------------------------------------- at most 8 rows: one launch
+// A projection of at most 8 rows as one launch: the RMSNorm of its input and
+// its epilogue included, no partials in memory. What bounds such a launch is
+// the time to fill the chip and one or two memory round trips, so everything
+// a block needs is asked for at once: 16 waves share a group of 8 weight rows
+// and split K evenly, each lane holding all of its 16-byte weight loads (PW)
+// before the first product; the waves' sums meet in LDS. The 16 x 16 tile of
+// the matrix core holds the even and odd 32-wide pieces of K side by side,
+// weight rows 0-7 / 8-15 and activation rows (columns) 0-7 / 8-15 of it, and
+// its two diagonal quadrants are added: 2048 outputs are 256 blocks, one per
+// CU, and a load covers whole 128-byte lines (the halves of K instead of its
+// pieces side by side: 13.5 us against 12.0 for 2048 x 11008).
+// A block of the norm forms walks groups blockIdx.x, + gridDim.x, ..., D groups'
+// loads in flight; one of the residual form takes one group.
+// Decode layer of the 3B drafter, 3 rows: product, reduce and norm launches 63
+// us, these four 42 us (QKV 6.7, O 4.5, gate/up 18.2 = 5.0 TB/s, down 12.0 =
+// 3.8 TB/s). Tiles of 16 whole rows for 9..16 activation rows were 2% slower
+// than those launches.
+enum { FEW_QKV, FEW_SWIGLU, FEW_RESIDUAL };
+struct FewArgs {
+  const f16 *A;      // FEW_RESIDUAL: activations [rows][AS K]
+  float *x;          // residual rows: the normed input, or the output
+  const bf16 *g;     // gain of the input's norm
+  float eps;
+  const uint16_t *W;
+  int rows, N, K;    // N weight rows
+  f16 *h;            // FEW_SWIGLU: [rows][AS N / 2]
+  int n_heads, n_kv;
+  QKVOut<f16> o;
+};
+
+// AS = 2: the activations are fp16 value + remainder (A and h rows [hi | lo]).
+template <int EPI, int AS, int PW, int D, bool WCVT, int WPE>
+__global__ __launch_bounds__(1024, WPE) void k_few(FewArgs a) {
+  constexpr int S = 128 + 4;  // LDS words per wave (+ 4: conflict-free column reads)
+  constexpr bool NORM = EPI != FEW_RESIDUAL;
+  __shared__ float red[2][16 * S];
+  __shared__ float ssq[16][8];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = (lane >> 3) & 1, lr = lane & 7;
+  const int hp = a.K / 64;            // pairs of 32-wide pieces
+  const int p0 = hp * w / 16, cnt = hp * (w + 1) / 16 - p0;
+  const int kbase = half * 32 + 8 * (lane >> 4);
+  const int ngroups = a.N / 8;
+  // K offset of the wave's pair j past the lane's own kbase (pairs past the
+  // slice re-load its last one and take no part in the products).
+  const auto koff = [&](int j) { return 64 * min(p0 + max(0, min(j, cnt - 1)), hp - 1); };
+  // Buffer loads: the lane's offset once, the pairs' in scalar registers.
+  const auto rsrc = [](const void *p, long bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes,
+                                             0x00020000);
+  };
+  const auto ld = [](__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
+    return __builtin_bit_cast(u32x4,
+                              __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
+  };
+  const __amdgpu_buffer_rsrc_t rw = rsrc(a.W, (long)a.N * a.K * 2);
+  const auto wrow = [&](int g) {      // weight row of this lane in group g
+    const int up = lr >> 2, i = lr & 3;
+    if constexpr (EPI == FEW_QKV)     // dims (d, d + 64) of a head slot
+      return (g >> 4) * 128 + (g & 15) * 4 + i + 64 * up;
+    else if constexpr (EPI == FEW_SWIGLU)
+      return g * 4 + i + up * (a.N / 2);
+    else
+      return g * 8 + lr;
+  };
+  const int arow = min(lr, a.rows - 1);
+
+  u32x4 wv[D][PW];
+  const auto load_w = [&](int i, int g, int j0) {
+    const uint32_t off = ((uint32_t)wrow(min(g, ngroups - 1)) * a.K + kbase) * 2;
+#pragma unroll
+    for (int j = 0; j < PW; ++j) wv[i][j] = ld(rw, off, 2 * koff(j0 + j));
+  };
+  const auto load_first = [&] {
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_w(i, blockIdx.x + i * gridDim.x, 0);
+  };
+  f16x8 af[PW][AS];
+  const auto load_a = [&](int j0) {
+    const __amdgpu_buffer_rsrc_t ra = rsrc(a.A, (long)a.rows * a.K * AS * 2);
+#pragma unroll
+    for (int j = 0; j < PW; ++j)
+#pragma unroll
+      for (int h = 0; h < AS; ++h)
+        af[j][h] = as_h8(ld(ra, (arow * AS * a.K + kbase) * 2, 2 * (koff(j0 + j) + h * a.K)));
+  };
+  // This thread's output (with its 15 neighbours): activation row r, weight
+  // row c of the group (q | k | v and gate / up: member c / 4 of pair c % 4, the
+  // members in neighbouring 16-lane rows).
+  const int r = tid >> 7, rc = min(r, a.rows - 1), c0 = (tid >> 4) & 7;
+  const int c = EPI == FEW_RESIDUAL ? c0 : (c0 >> 1) + 4 * (c0 & 1);
+  // What the epilogue needs from memory, asked for before the products (the
+  // position before all else: the rotary entries hang on it).
+  float xo = 0.f;
+  float2 cs = {1.f, 0.f};
+  int pos = 0, crow = 0;
+  if constexpr (EPI == FEW_QKV) {
+    pos = qkv_row_pos(a.o, rc);
+    crow = qkv_cache_row(a.o, rc);
+  }
+  const auto load_cs = [&](int g) { cs = a.o.rope[(long)pos * 64 + (g & 15) * 4 + (c0 >> 1)]; };
+  if constexpr (NORM) {
+    f32x4 xv[PW][2];
+    u32x4 gv[PW];
+    const __amdgpu_buffer_rsrc_t rx = rsrc(a.x, (long)a.rows * a.K * 4);
+    const __amdgpu_buffer_rsrc_t rg = rsrc(a.g, (long)a.K * 2);
+    const uint32_t off = (arow * a.K + kbase) * 4;
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      xv[j][0] = __builtin_bit_cast(f32x4, ld(rx, off, 4 * koff(j)));
+      xv[j][1] = __builtin_bit_cast(f32x4, ld(rx, off + 16, 4 * koff(j)));
+      gv[j] = ld(rg, kbase * 2, 2 * koff(j));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_first();
+    if constexpr (EPI == FEW_QKV) load_cs(blockIdx.x);
+    __builtin_amdgcn_sched_barrier(0);
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < PW; ++j)
+      if (j < cnt)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += xv[j][e >> 2][e & 3] * xv[j][e >> 2][e & 3];
+    ss += row_rotated<0x128>(ss);
+    auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(ss), __float_as_uint(ss), false,
+                                               false);
+    ss = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(ss), __float_as_uint(ss), false, false);
+    ss = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    if (lane < 8) ssq[w][lane] = ss;
+    __syncthreads();
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += ssq[i][lr];
+    const float rs = rsqrtf(t / (float)a.K + a.eps);
+#pragma unroll
+    for (int j = 0; j < PW; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t gw = gv[j][e >> 1];
+        const float gf = __uint_as_float(e & 1 ? gw & 0xFFFF0000u : gw << 16);
+        const float v = xv[j][e >> 2][e & 3] * rs * gf;
+        const f16 hi = static_cast<f16>(v);
+        af[j][0][e] = hi;
+        if constexpr (AS == 2) af[j][1][e] = static_cast<f16>(v - static_cast<float>(hi));
+      }
+  } else {
+    load_first();
+    load_a(0);
+    xo = a.x[(long)rc * a.N + blockIdx.x * 8 + c];
+  }
+
+  int buf = 0;
+  for (int g0 = blockIdx.x; g0 < ngroups; g0 += D * gridDim.x) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      const int g = g0 + i * gridDim.x;
+      if (g >= ngroups) break;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int j0 = 0;;) {
+#pragma unroll
+        for (int j = 0; j < PW; ++j)
+          if (j0 + j < cnt) {
+            const f16x8 wf = as_h8(WCVT ? sk_bf16_to_f16(wv[i][j]) : wv[i][j]);
+#pragma unroll
+            for (int h = 0; h < AS; ++h)
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, af[j][h], acc, 0, 0, 0);
+          }
+        if (NORM || (j0 += PW) >= cnt) break;
+        load_w(i, g, j0);
+        load_a(j0);
+      }
+      if (NORM && g + D * (int)gridDim.x < ngroups) load_w(i, g + D * gridDim.x, 0);
+      // Lane: activation row lane % 8, weight rows 4 (lane / 16 % 2) + 0..3 of
+      // quadrant (lane / 32, lane / 8 % 2).
+      if (half == lane >> 5)
+        *reinterpret_cast<f32x4 *>(&red[buf][w * S + half * 64 + lr * 8 + (lane >> 2 & 4)]) = acc;
+      __syncthreads();
+      const float *p = &red[buf][(tid & 15) * S + r * 8 + c];
+      float v = p[0] + p[64];
+      v += row_rotated<0x128>(v);
+      v += row_rotated<0x124>(v);
+      v += row_rotated<0x122>(v);
+      v += row_rotated<0x121>(v);
+      if constexpr (EPI == FEW_RESIDUAL) {
+        if ((tid & 15) == 0 && r < a.rows) a.x[(long)r * a.N + g * 8 + c] = xo + v;
+        return;
+      }
+      float v2 = __shfl_xor(v, 16, 64);
+      if ((tid & 31) == 0 && r < a.rows) {
+        if constexpr (EPI == FEW_SWIGLU) {
+          const int F = a.N / 2;
+          const float hv = v / (1.f + __expf(-v)) * v2;
+          const f16 hi = static_cast<f16>(hv);
+          f16 *hr = a.h + (long)r * F * AS + g * 4 + c;
+          *hr = hi;
+          if constexpr (AS == 2) hr[F] = static_cast<f16>(hv - static_cast<float>(hi));
+        } else {
+          const int slot = g >> 4;
+          qk_turn(a.o, a.n_heads, a.n_kv, slot, v, v2, cs);
+          qkv_store_at(a.o, a.n_heads, a.n_kv, slot, r, (g & 15) * 4 + c, v, v2, crow);
+        }
+      }
+      if (EPI == FEW_QKV && g + (int)gridDim.x < ngroups) load_cs(g + gridDim.x);
+      buf ^= 1;
+    }
+  }
+}
+
+template <int EPI, int AS, int PW, int D, int WPE>
+hipError_t launch_few(const FewArgs &a, bool w_f16, int most, hipStream_t s) {
+  const int blocks = std::min(a.N / 8, most);
+  if (w_f16)
+    k_few<EPI, AS, PW, D, false, WPE><<<blocks, 1024, 0, s>>>(a);
+  else
+    k_few<EPI, AS, PW, D, true, WPE><<<blocks, 1024, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+// Loads per lane of a weight row group.
+inline int few_loads(int K) { return (K / 64 + 15) / 16; }
+
+// The gate/up projection keeps two groups' loads in flight on two blocks a CU
+// (18.2 us for 22016 x 2048; one group 31.3, three 19.5, four on one block a CU
+// 19.2) where the registers allow it; the QKV projection's few groups are one
+// block a CU's worth (6.7 us for 2560 x 2048, 8.0 with two blocks a CU).
+template <int EPI>
+hipError_t launch_few_norm(const FewArgs &a, bool w_f16, int asplit, hipStream_t s) {
+  constexpr bool GU = EPI == FEW_SWIGLU;
+  constexpr int D = GU ? 2 : 1;
+  if (few_loads(a.K) <= 2) {
+    if (asplit == 2) return launch_few<EPI, 2, 2, D, 4>(a, w_f16, 256, s);
+    return launch_few<EPI, 1, 2, D, GU ? 8 : 4>(a, w_f16, GU ? 512 : 256, s);
+  }
+  return asplit == 2 ? launch_few<EPI, 2, 4, D, 4>(a, w_f16, 256, s)
+                     : launch_few<EPI, 1, 4, D, 4>(a, w_f16, 256, s);
+}
+
 template <int OUT, int RG, int AS, int NW = 1>
 hipError_t launch_rg(const f16 *A, int rows, const void *W, bool w_f16, int N, int K, int ks,
                      float *part, hipStream_t s, const int32_t *tgt, float *tgt_logit) {
@@ -383,6 +626,43 @@ hipError_t skinny_qkv_rope(const f16 *A, int rows, int asplit, const void *W, bo
   const long n = (long)rows * (n_heads + 2 * n_kv) * 64;
   k_skinny_qkv<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(part, ks, rows, n_heads, n_kv, out);
   return hipGetLastError();
+}
+
+bool few_ok(int rows, int d, int att, int F) {
+  // (The norm forms hold a wave's share of K in registers: 4 loads a lane. The
+  // residual forms take any K of whole 64s. Weight offsets are 32 bits.)
+  return rows >= 1 && rows <= 8 && d % 64 == 0 && few_loads(d) <= 4 && att % 64 == 0 &&
+         F % 64 == 0 && (size_t)std::max(2 * F, 3 * att) * d * 2 <= UINT32_MAX;
+}
+
+hipError_t few_qkv_rope(const float *x, const bf16 *g, float eps, int rows, int asplit,
+                        const void *W, bool w_f16, int K, int n_heads, int n_kv,
+                        const QKVOut<f16> &out, hipStream_t s) {
+  const FewArgs a{nullptr, const_cast<float *>(x), g, eps, static_cast<const uint16_t *>(W), rows,
+                  (n_heads + 2 * n_kv) * 128, K, nullptr, n_heads, n_kv, out};
+  return launch_few_norm<FEW_QKV>(a, w_f16, asplit, s);
+}
+
+hipError_t few_swiglu(const float *x, const bf16 *g, float eps, int rows, int asplit,
+                      const void *W, bool w_f16, int F, int K, f16 *h, hipStream_t s) {
+  const FewArgs a{nullptr, const_cast<float *>(x), g, eps, static_cast<const uint16_t *>(W), rows,
+                  2 * F, K, h, 0, 0, {}};
+  return launch_few_norm<FEW_SWIGLU>(a, w_f16, asplit, s);
+}
+
+hipError_t few_residual(const f16 *A, int rows, int asplit, const void *W, bool w_f16, int N,
+                        int K, float *x, hipStream_t s) {
+  const FewArgs a{A, x, nullptr, 0.f, static_cast<const uint16_t *>(W), rows, N, K, nullptr, 0, 0,
+                  {}};
+  constexpr int EPI = FEW_RESIDUAL, ALL = INT32_MAX;
+  const int loads = few_loads(K);
+  if (loads <= 2)
+    return asplit == 2 ? launch_few<EPI, 2, 2, 1, 8>(a, w_f16, ALL, s)
+                       : launch_few<EPI, 1, 2, 1, 8>(a, w_f16, ALL, s);
+  if (asplit == 2) return launch_few<EPI, 2, 6, 1, 4>(a, w_f16, ALL, s);
+  // More groups than CUs: two blocks a CU with fewer loads each.
+  if (loads <= 6 || N / 8 > 256) return launch_few<EPI, 1, 6, 1, 8>(a, w_f16, ALL, s);
+  return launch_few<EPI, 1, 11, 1, 4>(a, w_f16, ALL, s);
 }
 
 int skinny_lm_chunks(int vocab) { return vocab % SK_ROWS ? 0 : vocab / SK_ROWS; }

@@ -419,8 +419,10 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
     // first split_mlp_layers layers.
     const int spm = kMfma && l < cf.split_mlp_layers ? 2 : 1;
     const TW *attn_g = static_cast<const TW *>(c->attn_norm[l]);
+    // Few rows: one launch per projection, norms and epilogues included.
+    const bool few_qkv = kMfma && few_ok(rows, d, Hq * hd, F);
     if constexpr (kMfma) {  // (the fp32 projections apply the norms themselves)
-      if (!xn_ready)
+      if (!xn_ready && !few_qkv)
         STAGE(c, K_NORM, "attention norm",
               launch_rmsnorm<TW, TA>(x, attn_g, rows, d, cf.rms_eps, xn, sp, s));
       xn_ready = false;
@@ -469,7 +471,10 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
       }
     }
     if constexpr (kMfma) {
-      if (rows <= kSkinnyMaxRows)
+      if (few_qkv)
+        STAGE(c, K_QKV, "qkv projection",
+              few_qkv_rope(x, attn_g, cf.rms_eps, rows, sp, wqkv, wf16, d, Hq, Hkv, qo, s));
+      else if (rows <= kSkinnyMaxRows)
         STAGE(c, K_QKV, "qkv projection",
               skinny_qkv_rope(xn, rows, sp, wqkv, wf16, d, Hq, Hkv, qo, gpart, s));
       else
@@ -566,6 +571,15 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
     float *x_r = x + (size_t)r0 * d;
     const TW *ffn_g = static_cast<const TW *>(c->ffn_norm[l]);
     if constexpr (kMfma) {
+      if (few_ok(nr, d, Hq * hd, F)) {
+        STAGE(c, tail ? K_TAIL : K_OPROJ, "output projection",
+              few_residual(attn_r, nr, sp, wo, wf16, d, Hq * hd, x_r, s));
+        STAGE(c, tail ? K_TAIL : K_GATEUP, "gate/up projection",
+              few_swiglu(x_r, ffn_g, cf.rms_eps, nr, spm, wgu, wf16, F, d, h, s));
+        STAGE(c, tail ? K_TAIL : K_DOWN, "down projection",
+              few_residual(h, nr, spm, wdown, wf16, d, F, x_r, s));
+        continue;
+      }
       if (nr <= kSkinnyMaxRows) {
         // Output projection + residual + FFN norm; gate/up + SwiGLU; down
         // projection + residual (+ the next layer's attention norm). The

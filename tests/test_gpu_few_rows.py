@@ -1,8 +1,8 @@
-"""The LM head of few rows (up to 32: a stream over the weights) beside the
+"""Few rows. The LM head of up to 32 (a stream over the weights) beside the
 tiled one: both sides of the line, one and two row groups, the three chunk
 forms of the vocabulary (multiples of 128, of 64, neither), and both weight
 storages, which must agree bit for bit. Bar: 2e-2 per token, the bar of the
-fp16-operand path."""
+fp16-operand path. The layers of up to 8 rows."""
 import numpy as np
 import pytest
 
@@ -42,3 +42,43 @@ def test_lm_head_of_few_rows(vocab, lens):
                                              wl.cand_ids, lens)
     assert np.abs(out[0][0] - ref).max() <= 2e-2
     assert int(out[0][2][0]) == am or abs(sc[0] - sc[1]) < 0.1
+
+
+# (d_model, heads, d_ff): the loads a wave's lanes make per weight row and the
+# waves left without any: 4 pairs of K for 16 waves; a long down projection on
+# few outputs; more than 256 output groups in several steps.
+@pytest.mark.parametrize("d, hq, ff", [(256, 2, 320), (256, 2, 6464), (2112, 3, 7104)])
+@pytest.mark.parametrize("prefix, lens", [(40, [1, 0]), (40, [7, 1]), (40, [8, 1]), (4, [3, 0])])
+def test_layers_of_few_rows(d, hq, ff, prefix, lens):
+    """Layers of up to 8 rows in one launch per projection (8 and 9 rows: both
+    sides of the line; 4 prefix rows: the fused pass itself is one), with split
+    operands in no, the attention's and both halves of the first layer. Fused
+    and two-call passes and both storages run the same products."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = W.VerifierConfig(
+        name=f"few rows d{d} F{ff}", n_layers=2, d_model=d, n_heads=hq, n_kv_heads=1,
+        head_dim=128, d_ff=ff, vocab=512, rope_base=1e6, dtype=W.BF16, n_prefix=prefix,
+        n_visual=2, n_cands=2, cand_len=8)
+    wl = W.make_workload(cfg, sum(lens), device="cuda")
+    for m in range(2):
+        wl.cand_ids[m, lens[m]:] = 0
+    lens = np.asarray(lens, dtype=np.int32)
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    ref, sc, am = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights),
+                                             W.to_host_f32(wl.visual), wl.prefix_ids,
+                                             wl.cand_ids, lens)
+    for split in ((0, 0), (1, 0), (2, 1)):
+        out = []
+        for storage in ("f16", "bf16"):
+            v = Verifier(cfg, wl.weights, device="cuda", gemm_weights=storage,
+                         split_layers=split[0], split_mlp_layers=split[1])
+            out.append(v.verify(wl.visual, ids, cids, lens)[0].cpu().numpy())
+            v.prefill(wl.visual, ids)
+            out.append(v.score(cids, lens)[0].cpu().numpy())
+        np.testing.assert_array_equal(out[0], out[2])
+        np.testing.assert_array_equal(out[1], out[3])
+        assert max(np.abs(o - ref).max() for o in out) <= 2e-2, split
