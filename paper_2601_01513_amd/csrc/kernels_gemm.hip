@@ -369,16 +369,24 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u;
 }
 
+// fp16 remainder of v. Not to be fused into the product that gave v: some
+// kernels' epilogues were and some not, and the 8- and four-wave forms of a
+// split product (bf16 and fp16 weights) differed in the last bits.
+__device__ __forceinline__ f16 rest_f16(float v, f16 hi) {
+#pragma clang fp contract(off)
+  return static_cast<f16>(v - static_cast<float>(hi));
+}
+
 // Activation store: fp16 value at base + col; with split = 2 also its fp16
 // remainder at base + n + col (row layout [hi | lo]).
 __device__ __forceinline__ void store_act(f16 *p, long base, int col, int n, int split, float v) {
   const f16 hi = static_cast<f16>(v);
   p[base + col] = hi;
-  if (split == 2) p[base + n + col] = static_cast<f16>(v - static_cast<float>(hi));
+  if (split == 2) p[base + n + col] = rest_f16(v, hi);
 }
 
 // ------------------------------------------------------- residual (O, down)
-// x += acc for one wave's NI x 4 MFMA blocks: this lane holds rows r0 + dr
+// x += acc for one wave's NI x NJ MFMA blocks: this lane holds rows r0 + dr
 // (dr = 32 i + 8 (r / 4) + r % 4 for block row i, register r) of columns
 // c0 + 32 j (block column j). Buffer loads and stores over x (rows * N * 4
 // bytes < 2 GiB, checked at launch): the lane offset carries the row, so
@@ -522,8 +530,7 @@ __global__ __launch_bounds__(NT) void k_gemm_swiglu(const f16 *__restrict__ A,
           *reinterpret_cast<f16x2 *>(h + base) = f16x2{h0, h1};
           if (asplit == 2)
             *reinterpret_cast<f16x2 *>(h + base + F) =
-                f16x2{static_cast<f16>(v0 - static_cast<float>(h0)),
-                      static_cast<f16>(v1 - static_cast<float>(h1))};
+                f16x2{rest_f16(v0, h0), rest_f16(v1, h1)};
         }
     }
     return;
@@ -737,8 +744,7 @@ __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ 
           *reinterpret_cast<f16x2 *>(dst) = f16x2{h0, h1};
           if (AS == 2)
             *reinterpret_cast<f16x2 *>(dst + F) =
-                f16x2{static_cast<f16>(v0 - static_cast<float>(h0)),
-                      static_cast<f16>(v1 - static_cast<float>(h1))};
+                f16x2{rest_f16(v0, h0), rest_f16(v1, h1)};
         }
     }
     return;
