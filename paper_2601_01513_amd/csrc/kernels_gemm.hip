@@ -41,7 +41,7 @@ namespace vsr {
 namespace {
 
 constexpr int BK = 64;        // K elements per panel (8 chunks of 16 bytes per row)
-constexpr int NT = 512;       // threads per block
+constexpr int NT = 512;       // threads per block (eight-wave tiles)
 constexpr int NWAVES = NT / 64;
 
 template <int BM_, int BN_, int WM_, int WN_>
@@ -50,7 +50,7 @@ struct Tile {
   static constexpr int TM = BM / WM, TN = BN / WN;  // wave sub-tile
   static constexpr int FM = TM / 32, FN = TN / 32;  // MFMA blocks per wave
   static constexpr int STAGE = (BM + BN) * 8;       // 16-byte chunks per LDS stage
-  static_assert(WM * WN == NWAVES, "eight waves");
+  static constexpr int NW = WM * WN;                // waves
   static_assert(TM % 32 == 0 && TN % 32 == 0, "32x32 MFMA blocks");
   static_assert(BM % 64 == 0 && BN % 64 == 0, "operand loads cover 64-row groups");
 };
@@ -59,6 +59,12 @@ struct Tile {
 // attention head (QKV) or 64 gate + 64 up columns (SwiGLU), so the rotary
 // pairs and the gate/up pairs sit in the same lane and register.
 typedef Tile<256, 256, 4, 2> TileStd;
+
+// 128 x 128 tile, four waves of 64 x 64, a ring of five stages (all 160 KB of
+// LDS): for products with too few 256 x 256 tiles to fill the chip without
+// splitting K (small_tiles).
+typedef Tile<128, 128, 2, 2> TileSmall;
+constexpr int kSmallStages = 5;
 
 __device__ __forceinline__ int swz(int row, int c) { return row * 8 + (c ^ ((row >> 1) & 7)); }
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
@@ -78,9 +84,10 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(u32x4 v) {
 
 // One operand (ROWS rows of a panel). CVT: stored as bf16, staged through
 // registers and converted; otherwise fp16, loaded straight into LDS.
-template <int ROWS, bool CVT>
+template <int ROWS, bool CVT, int NW>
 struct Operand {
-  static constexpr int PER_THREAD = ROWS * 8 / NT;  // 16-byte chunks per thread
+  static constexpr int NTH = NW * 64;
+  static constexpr int PER_THREAD = ROWS * 8 / NTH;  // 16-byte chunks per thread
   const uint16_t *g[PER_THREAD];                     // row base + chunk, K-tile 0
   int slot[PER_THREAD];                              // LDS chunk (register path)
   u32x4 r[CVT ? PER_THREAD : 1];
@@ -93,15 +100,15 @@ struct Operand {
     for (int i = 0; i < PER_THREAD; ++i) {
       int row, c;
       if constexpr (CVT) {
-        const int id = i * NT + t;
+        const int id = i * NTH + t;
         row = id >> 3;
         c = id & 7;
         slot[i] = swz(row, c);
       } else {
-        // Direct load i of wave w fills LDS rows 8 (i * NWAVES + w) .. +7;
+        // Direct load i of wave w fills LDS rows 8 (i * NW + w) .. +7;
         // lane l lands in physical chunk l % 8 of row l / 8.
         const int w = t >> 6, l = t & 63;
-        row = (i * NWAVES + w) * 8 + (l >> 3);
+        row = (i * NW + w) * 8 + (l >> 3);
         c = (l & 7) ^ ((row >> 1) & 7);
         slot[i] = 0;
       }
@@ -116,7 +123,7 @@ struct Operand {
         r[i] = *reinterpret_cast<const u32x4 *>(g[i] + kt * BK);
       } else {
         const int w = threadIdx.x >> 6;
-        __builtin_amdgcn_global_load_lds(g[i] + kt * BK, dst + (i * NWAVES + w) * 64, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(g[i] + kt * BK, dst + (i * NW + w) * 64, 16, 0, 0);
       }
     }
   }
@@ -140,7 +147,12 @@ struct Frags {
 #pragma unroll
     for (int fn = 0; fn < TL::FN; ++fn) b[fn] = as_f16x8(stage[swz(fb[fn], c)]);
   }
-  __device__ __forceinline__ void mma(f32x16 (&acc)[TL::FM][TL::FN]) const {
+  template <bool CVT_B = false>
+  __device__ __forceinline__ void mma(f32x16 (&acc)[TL::FM][TL::FN]) {
+    if constexpr (CVT_B)
+#pragma unroll
+      for (int fn = 0; fn < TL::FN; ++fn)
+        b[fn] = as_f16x8(bf16x8_to_f16x8(__builtin_bit_cast(u32x4, b[fn])));
 #pragma unroll
     for (int fm = 0; fm < TL::FM; ++fm)
 #pragma unroll
@@ -173,8 +185,8 @@ __device__ __forceinline__ void mainloop(const void *A, ARow arow, const void *B
   const int nkb = K / BK;  // K panels of B
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wm = w / TL::WN, wn = w % TL::WN;
-  Operand<TL::BM, CVT_A> oa;
-  Operand<TL::BN, CVT_B> ob;
+  Operand<TL::BM, CVT_A, TL::NW> oa;
+  Operand<TL::BN, CVT_B, TL::NW> ob;
   oa.init(A, (long)K * asplit, arow);
   ob.init(B, K, brow);
 #pragma unroll
@@ -226,6 +238,71 @@ __device__ __forceinline__ void mainloop(const void *A, ARow arow, const void *B
     __syncthreads();
     if (more) f0.load(nxt, fa, fb, hc);
   }
+}
+
+// The same on a ring of NS LDS stages, panels loaded NS - 1 ahead: with one
+// panel ahead a small tile's 0.25 us of products per panel waited out a memory
+// round trip of about 1 us each (O projection of the 1.5B shape, 2048 rows: 24
+// us, now 20; reading a whole panel's fragments ahead as well gave 23). Both operands
+// go straight to LDS; CVT_B: bf16 values, converted as the fragments are read.
+// vmcnt counts the panels still in flight (loads return in order): at panel k
+// those behind it, up to NS - 2, may be. The barrier then shows every wave's
+// part of panel k landed and every read of panel k - 1 done (lgkmcnt), whose
+// stage the next load overwrites.
+template <class TL, int NS, bool CVT_B, class ARow, class BRow>
+__device__ __forceinline__ void mainloop_ring(const void *A, ARow arow, const void *B, BRow brow,
+                                              int K, int asplit, u32x4 *lds,
+                                              f32x16 (&acc)[TL::FM][TL::FN]) {
+  const int nkb = K / BK, n = nkb * asplit;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wm = w / TL::WN, wn = w % TL::WN;
+  Operand<TL::BM, false, TL::NW> oa;
+  Operand<TL::BN, false, TL::NW> ob;
+  constexpr int LOADS = oa.PER_THREAD + ob.PER_THREAD;
+  static_assert(LOADS * (NS - 2) <= 63, "vmcnt");
+  oa.init(A, (long)K * asplit, arow);
+  ob.init(B, K, brow);
+  int fa[TL::FM], fb[TL::FN];
+#pragma unroll
+  for (int fm = 0; fm < TL::FM; ++fm) {
+    fa[fm] = wm * TL::TM + fm * 32 + (lane & 31);
+#pragma unroll
+    for (int fn = 0; fn < TL::FN; ++fn) acc[fm][fn] = f32x16{};
+  }
+#pragma unroll
+  for (int fn = 0; fn < TL::FN; ++fn) fb[fn] = TL::BM + wn * TL::TN + fn * 32 + (lane & 31);
+  const int hc = lane >> 5;
+  constexpr int NR = TL::FM + TL::FN, NM = TL::FM * TL::FN;
+  const auto issue = [&](int k, u32x4 *dst) {
+    oa.issue(k, dst);
+    ob.issue(k >= nkb ? k - nkb : k, dst + TL::BM * 8);
+  };
+  for (int k = 0; k < min(n, NS - 1); ++k) issue(k, lds + k * TL::STAGE);
+  Frags<TL> f0{}, f1{};
+  int rd = 0;
+  for (int k = 0; k < n; ++k) {
+    if (n - 1 - k >= NS - 2)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS * (NS - 2)) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const u32x4 *cur = lds + rd * TL::STAGE;
+    if (k + NS - 1 < n) issue(k + NS - 1, lds + (rd == 0 ? NS - 1 : rd - 1) * TL::STAGE);
+    f0.load(cur, fa, fb, hc);
+    f1.template mma<CVT_B>(acc);  // the last k-step of the panel before (zeros at first)
+    interleave_reads(NR, NM);
+    f1.load(cur, fa, fb, 2 + hc);
+    f0.template mma<CVT_B>(acc);
+    interleave_reads(NR, NM);
+    f0.load(cur, fa, fb, 4 + hc);
+    f1.template mma<CVT_B>(acc);
+    interleave_reads(NR, NM);
+    f1.load(cur, fa, fb, 6 + hc);
+    f0.template mma<CVT_B>(acc);
+    interleave_reads(NR, NM);
+    rd = rd == NS - 1 ? 0 : rd + 1;
+  }
+  f1.template mma<CVT_B>(acc);
+  __syncthreads();  // every wave is past its last LDS reads
 }
 
 // Output row / column (within the block tile) of accumulator register r of
@@ -397,14 +474,14 @@ __device__ __forceinline__ void store_act(f16 *p, long base, int col, int n, int
 // per-element 64-bit addresses spilled registers. Batches of 8 rows x 4
 // column blocks (32 values) are loaded before any of them is stored (the
 // compiler cannot move a load of x above a store to x).
-template <int NI>
-__device__ __forceinline__ void residual_epilogue(const f32x16 (&acc)[NI][4], int r0, int c0,
+template <int NI, int NJ>
+__device__ __forceinline__ void residual_epilogue(const f32x16 (&acc)[NI][NJ], int r0, int c0,
                                                   int rows, int N, float *x) {
   const __amdgpu_buffer_rsrc_t xr =
       __builtin_amdgcn_make_buffer_rsrc(x, (short)0, (int)((size_t)rows * N * 4), 0x00020000);
-  uint32_t bx[4];
+  uint32_t bx[NJ];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int col = c0 + 32 * j;
     bx[j] = col < N ? (uint32_t)(r0 * N + col) * 4u : 0x80000000u;
   }
@@ -412,12 +489,12 @@ __device__ __forceinline__ void residual_epilogue(const f32x16 (&acc)[NI][4], in
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int rh = 0; rh < 2; ++rh) {
-      float xv[8][4];
+      float xv[8][NJ];
       // (the b32 buffer builtins move raw bits: bit-cast, not convert)
 #pragma unroll
       for (int rr = 0; rr < 8; ++rr)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < NJ; ++j) {
           const uint32_t dr = 32 * i + 16 * rh + 8 * (rr >> 2) + (rr & 3);
           xv[rr][j] = __uint_as_float(
               __builtin_amdgcn_raw_buffer_load_b32(xr, bx[j] + dr * (uint32_t)N * 4u, 0, 0));
@@ -426,7 +503,7 @@ __device__ __forceinline__ void residual_epilogue(const f32x16 (&acc)[NI][4], in
       for (int rr = 0; rr < 8; ++rr) {
         const uint32_t dr = 32 * i + 16 * rh + 8 * (rr >> 2) + (rr & 3);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(xv[rr][j] + acc[i][j][8 * rh + rr]),
                                                 xr, bx[j] + dr * (uint32_t)N * 4u, 0, 0);
       }
@@ -456,8 +533,27 @@ __global__ __launch_bounds__(NT) void k_gemm_residual(const f16 *__restrict__ A,
   static_assert(TL::FN == 4 && TL::TN == 128, "four 32-column blocks per wave");
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w / TL::WN, wn = w % TL::WN;
-  residual_epilogue<TL::FM>(acc, m0 + wm * TL::TM + 4 * (lane >> 5), n0 + wn * TL::TN + (lane & 31),
+  residual_epilogue(acc, m0 + wm * TL::TM + 4 * (lane >> 5), n0 + wn * TL::TN + (lane & 31),
                             rows, N, x);
+}
+
+// The same on the small tile, whole K.
+template <class TL, bool WCVT>
+__global__ __launch_bounds__(TL::NW * 64) void k_gemm_residual_s(const f16 *__restrict__ A,
+                                                                 const uint16_t *__restrict__ W,
+                                                                 int rows, int N, int K,
+                                                                 int asplit, Launch ln,
+                                                                 float *__restrict__ x) {
+  __shared__ u32x4 lds[kSmallStages * TL::STAGE];
+  const Work wk = block_work(ln);
+  const int m0 = wk.tm * TL::BM, n0 = wk.tn * TL::BN;
+  f32x16 acc[TL::FM][TL::FN];
+  mainloop_ring<TL, kSmallStages, WCVT>(
+      A, [=](int r) { return min(m0 + r, rows - 1); }, W,
+      [=](int r) { return min(n0 + r, N - 1); }, K, asplit, lds, acc);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  residual_epilogue(acc, m0 + w / TL::WN * TL::TM + 4 * (lane >> 5),
+                    n0 + w % TL::WN * TL::TN + (lane & 31), rows, N, x);
 }
 
 // Tail tiles: x += sum of the partials. Block (tail tile, 256-element slab).
@@ -690,7 +786,7 @@ __global__ __launch_bounds__(256) void k_gemm_residual_4w(const f16 *__restrict_
     return;
   }
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
-  residual_epilogue<4>(acc, m0 + wm * 128 + 4 * (lane >> 5), n0 + wn * 128 + (lane & 31), rows, N,
+  residual_epilogue(acc, m0 + wm * 128 + 4 * (lane >> 5), n0 + wn * 128 + (lane & 31), rows, N,
                        x);
 }
 
@@ -978,6 +1074,83 @@ __global__ __launch_bounds__(NT) void k_gemm_qkv(const f16 *__restrict__ A,
     }
   }
   if (staged) qk_copy_out<16>(stg, o, n_heads, slot, r0, rows, 0);
+}
+
+// The same on the small tile, whole K: a block is one head slot of 128 rows.
+// Wave column wn takes dims 32 wn .. + 31 and the 32 that they rotate with, so
+// a pair sits in one lane (MFMA blocks 0 and 1); the two waves of a row half
+// share its staging block.
+template <class TL, bool WCVT>
+__global__ __launch_bounds__(TL::NW * 64) void k_gemm_qkv_s(const f16 *__restrict__ A,
+                                                            const uint16_t *__restrict__ W,
+                                                            int rows, int K, int asplit,
+                                                            int n_heads, int n_kv, Launch ln,
+                                                            QKVOut<f16> o) {
+  static_assert(TL::TM == 64 && TL::TN == 64 && TL::BN == 128, "a rotary pair per lane");
+  static_assert(kSmallStages * TL::STAGE >= TL::WM * 1024, "a 16 KB staging block per wave row");
+  __shared__ u32x4 lds[kSmallStages * TL::STAGE];
+  const Work wk = block_work(ln);
+  const int m0 = wk.tm * TL::BM, slot = wk.tn;
+  f32x16 acc[TL::FM][TL::FN];
+  mainloop_ring<TL, kSmallStages, WCVT>(
+      A, [=](int r) { return min(m0 + r, rows - 1); }, W,
+      [=](int r) { return slot * 128 + (r >> 6) * 32 + (r & 31) + (r & 32) * 2; }, K, asplit,
+      lds, acc);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wm = w / TL::WN, wn = w % TL::WN;
+  const int r0 = m0 + wm * TL::TM, d = 32 * wn + (lane & 31);
+  const bool precise = o.q_lo || o.k_lo || o.vt_lo, value = slot >= n_heads + n_kv;
+  f16 *stg = reinterpret_cast<f16 *>(lds + wm * 1024);
+  VtBlock vb;
+  const bool staged =
+      !precise && (value ? vt_block(o, n_heads, n_kv, slot, r0, rows, vb) : qk_staged_ok(o));
+#pragma unroll
+  for (int fm = 0; fm < TL::FM; ++fm) {
+    if (value && staged) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f16x4 a, b;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          a[j] = static_cast<f16>(acc[fm][0][4 * q + j]);
+          b[j] = static_cast<f16>(acc[fm][1][4 * q + j]);
+        }
+        const int p = 32 * fm + 16 * (q >> 1) + 8 * (lane >> 5) + 4 * (q & 1);
+        *reinterpret_cast<f16x4 *>(stg + stg_vt(d, p)) = a;
+        *reinterpret_cast<f16x4 *>(stg + stg_vt(d + 64, p)) = b;
+      }
+      continue;
+    }
+    // The rotary entries of all 16 rows before any store, as above.
+    float2 cs[16];
+    if (!value) {
+      int pos[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        pos[r] = qkv_row_pos(o, min(m0 + acc_row<TL>(wm, fm, r, lane), rows - 1));
+#pragma unroll
+      for (int r = 0; r < 16; ++r) cs[r] = o.rope[(long)pos[r] * 64 + d];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = m0 + acc_row<TL>(wm, fm, r, lane);
+      float x1 = acc[fm][0][r], x2 = acc[fm][1][r];
+      if (!value) qk_turn(o, n_heads, n_kv, slot, x1, x2, cs[r]);
+      if (staged) {
+        const int sr = acc_row<TL>(0, fm, r, lane);
+        stg[stg_row(sr, d)] = static_cast<f16>(x1);
+        stg[stg_row(sr, d + 64)] = static_cast<f16>(x2);
+      } else if (row < rows) {
+        qkv_store_rotated(o, n_heads, n_kv, slot, row, d, x1, x2);
+      }
+    }
+  }
+  __syncthreads();
+  if (!staged) return;
+  if (value)
+    vt_copy_out<8>(stg, vb.vt, vb.npos, vb.crow0, 8 * wn);
+  else
+    qk_copy_out<8>(stg, o, n_heads, slot, r0, rows, 8 * wn);
 }
 
 // Tail tiles: the partials summed in split order, then the rotary and the
@@ -1346,10 +1519,30 @@ inline bool four_wave_ok(bool w_f16, int asplit, int rows, int nrows_w, int K) {
   do {                                                                           \
     const uint16_t *W16 = static_cast<const uint16_t *>(W);                      \
     if (w_f16)                                                                   \
-      kern<TL, false><<<grid, NT, 0, s>>>(__VA_ARGS__);                           \
+      kern<TL, false><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                           \
     else                                                                         \
-      kern<TL, true><<<grid, NT, 0, s>>>(__VA_ARGS__);                            \
+      kern<TL, true><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                            \
   } while (0)
+
+// Launch of the small-tile form, or an empty one where the 256 x 256 tiles are
+// the better form (`base`: us of a small launch beside its panels). A small tile
+// takes its panels at the rate one CU loads them, 0.62 us each (0.75 with bf16
+// weights), whatever the number of blocks up to one a CU; a split launch about
+// 12 us (two launches, the reduce's round trips), 1.2 us per panel of a block
+// and 0.085 us per block for its partial tile (256 KB written and read). The line
+// lies where both weight storages gain, as both take the same form and score
+// alike. Measured, split and reduce / small (us, fp16; bf16 weights): O of 1.5B
+// at 512 rows 22/16; 23/21, at 1024 24/18; 23/22, at 2048 34/20; 32/23, at 3072
+// (two rounds) 38/35; 36/42; O of 3B at 1024 35/23; 31/29; O of 7B at 640 43/37;
+// 39/45; QKV of 1.5B at 1024 28/24; 27/29, at 2048 38/27; 35/31.
+Launch small_tiles(int rows, int N, int K, int asplit, float base) {
+  const int nm = (rows + 127) / 128, nn = (N + 127) / 128, nk = K / BK * asplit;
+  const Launch big = plan_launch((rows + 255) / 256, (N + 255) / 256, 8, nk);
+  const float t_small = base + 0.8f * nk;
+  const float t_big = 12.f + 1.2f * nk / big.nsplit + 0.085f * big.ntail * big.nsplit;
+  if (big.ndp > 0 || nm * nn > 256 || t_small >= t_big) return Launch{0, 0, 1, 0, 0, 1};
+  return Launch{nm, nn, 8, nm * nn, 0, 1};
+}
 
 hipError_t gemm_residual(const f16 *A, const void *W, bool w_f16, int rows, int N, int K,
                          int asplit, float *x, float *part, hipStream_t s) {
@@ -1358,6 +1551,11 @@ hipError_t gemm_residual(const f16 *A, const void *W, bool w_f16, int rows, int 
   // Both residual epilogues address x through buffer descriptors of 32-bit
   // byte ranges.
   if ((size_t)rows * N * 4 > INT32_MAX) return hipErrorInvalidValue;
+  if (const Launch ls = small_tiles(rows, N, K, asplit, 5.f); ls.ndp > 0) {
+    typedef TileSmall TL;
+    VSR_WLAUNCH(k_gemm_residual_s, ls.blocks(), A, W16, rows, N, K, asplit, ls, x);
+    return hipGetLastError();
+  }
   const Launch ln = plan_launch((rows + TL::BM - 1) / TL::BM, (N + TL::BN - 1) / TL::BN, 8,
                                 K / BK * asplit);
   const int fw = K * asplit >= kFourWaveMinK ? 2 : 4;
@@ -1398,6 +1596,11 @@ hipError_t gemm_qkv_rope(const f16 *A, const void *W, bool w_f16, int rows, int 
   if (rows == 0) return hipSuccess;
   typedef TileStd TL;
   const int nslots = n_heads + 2 * n_kv;
+  if (const Launch ls = small_tiles(rows, nslots * 128, K, asplit, 14.f); ls.ndp > 0) {
+    typedef TileSmall TL;
+    VSR_WLAUNCH(k_gemm_qkv_s, ls.blocks(), A, W16, rows, K, asplit, n_heads, n_kv, ls, out);
+    return hipGetLastError();
+  }
   const Launch ln = plan_launch((rows + TL::BM - 1) / TL::BM, (nslots + 1) / 2, 8,
                                 K / BK * asplit);
   VSR_WLAUNCH(k_gemm_qkv, ln.blocks(), A, W16, rows, K, asplit, n_heads, n_kv, ln, out, part);
