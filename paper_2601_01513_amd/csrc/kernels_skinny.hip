@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void k_skinny_qkv(const float *__restrict__ pa
 // A block of the norm forms walks groups blockIdx.x, + gridDim.x, ..., D groups'
 // loads in flight; one of the residual form takes one group.
 // Decode layer of the 3B drafter, 3 rows: product, reduce and norm launches 63
-// us, these four 42 us (QKV 6.7, O 4.5, gate/up 18.2 = 5.0 TB/s, down 12.0 =
+// us, these four 42 us (QKV 7.4, O 4.6, gate/up 18.2 = 5.0 TB/s, down 11.9 =
 // 3.8 TB/s). Tiles of 16 whole rows for 9..16 activation rows were 2% slower
 // than those launches.
 enum { FEW_QKV, FEW_SWIGLU, FEW_RESIDUAL };
@@ -519,7 +519,7 @@ inline int few_loads(int K) { return (K / 64 + 15) / 16; }
 // The gate/up projection keeps two groups' loads in flight on two blocks a CU
 // (18.2 us for 22016 x 2048; one group 31.3, three 19.5, four on one block a CU
 // 19.2) where the registers allow it; the QKV projection's few groups are one
-// block a CU's worth (6.7 us for 2560 x 2048, 8.0 with two blocks a CU).
+// block a CU's worth (7.4 us for 2560 x 2048, about 1.3 more with two blocks a CU).
 template <int EPI>
 hipError_t launch_few_norm(const FewArgs &a, bool w_f16, int asplit, hipStream_t s) {
   constexpr bool GU = EPI == FEW_SWIGLU;

@@ -419,8 +419,14 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
     // first split_mlp_layers layers.
     const int spm = kMfma && l < cf.split_mlp_layers ? 2 : 1;
     const TW *attn_g = static_cast<const TW *>(c->attn_norm[l]);
-    // Few rows: one launch per projection, norms and epilogues included.
-    const bool few_qkv = kMfma && few_ok(rows, d, Hq * hd, F);
+    const TW *ffn_g = static_cast<const TW *>(c->ffn_norm[l]);
+    // Few rows: one launch per projection, norms and epilogues included (they
+    // read the gains 16 bytes at a time; the other forms take any address).
+    const auto few = [&](int n) {
+      return kMfma && few_ok(n, d, Hq * hd, F) &&
+             ((reinterpret_cast<uintptr_t>(attn_g) | reinterpret_cast<uintptr_t>(ffn_g)) & 15) == 0;
+    };
+    const bool few_qkv = few(rows);
     if constexpr (kMfma) {  // (the fp32 projections apply the norms themselves)
       if (!xn_ready && !few_qkv)
         STAGE(c, K_NORM, "attention norm",
@@ -569,9 +575,8 @@ int run_layers(vsr_ctx *c, int rows, int mode, const Split &split) {
     }
     const TA *attn_r = attn + (size_t)r0 * Hq * hd * sp;
     float *x_r = x + (size_t)r0 * d;
-    const TW *ffn_g = static_cast<const TW *>(c->ffn_norm[l]);
     if constexpr (kMfma) {
-      if (few_ok(nr, d, Hq * hd, F)) {
+      if (few(nr)) {
         STAGE(c, tail ? K_TAIL : K_OPROJ, "output projection",
               few_residual(attn_r, nr, sp, wo, wf16, d, Hq * hd, x_r, s));
         STAGE(c, tail ? K_TAIL : K_GATEUP, "gate/up projection",

@@ -82,3 +82,30 @@ def test_layers_of_few_rows(d, hq, ff, prefix, lens):
         np.testing.assert_array_equal(out[0], out[2])
         np.testing.assert_array_equal(out[1], out[3])
         assert max(np.abs(o - ref).max() for o in out) <= 2e-2, split
+
+
+def test_gains_at_any_address():
+    """Norm gains that start 2 bytes into an allocation: the rows that read them
+    16 bytes at a time otherwise take the form that does not."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = W.VerifierConfig(
+        name="gains off 16 bytes", n_layers=2, d_model=256, n_heads=2, n_kv_heads=1,
+        head_dim=128, d_ff=320, vocab=512, rope_base=1e6, dtype=W.BF16, n_prefix=20,
+        n_visual=2, n_cands=1, cand_len=6)
+    wl = W.make_workload(cfg, 3, device="cuda")
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    ref, _, _ = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights),
+                                           W.to_host_f32(wl.visual), wl.prefix_ids, wl.cand_ids,
+                                           wl.cand_len)
+    for lw in wl.weights["layers"]:
+        for k in ("attn_norm", "ffn_norm"):
+            off = torch.empty(cfg.d_model + 1, dtype=lw[k].dtype, device="cuda")[1:]
+            lw[k] = off.copy_(lw[k])
+            assert lw[k].data_ptr() % 16 == 2
+    v = Verifier(cfg, wl.weights, device="cuda")
+    v.prefill(wl.visual, ids)
+    assert np.abs(v.score(cids, wl.cand_len)[0].cpu().numpy() - ref).max() <= 2e-2
