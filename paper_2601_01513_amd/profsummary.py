@@ -42,10 +42,16 @@ def _short(name: str) -> str:
         base = "k_attn<2> (draft" + (", precise)" if precise else
                                      ", decode blocks)" if dec else ")")
     elif base == "k_skinny":
-        # k_skinny<rows per group, A split, bf16 weights, greedy LM head>
-        m = re.search(r"k_skinnyILi(\d+)ELi(\d+)ELb(\d)ELb(\d)E", name)
+        # k_skinny<rows per group, A split, bf16 weights, output, row groups>
+        m = re.search(r"k_skinnyILi(\d+)ELi(\d+)ELb(\d)ELi(\d)E", name)
         if m:
-            base = "k_skinny (" + ("greedy LM head" if m.group(4) == "1" else "product") + \
+            base = "k_skinny (" + ("product", "greedy LM head", "LM head")[int(m.group(4))] + \
+                (", split A" if m.group(2) == "2" else "") + ")"
+    elif base == "k_few":
+        # k_few<projection, A split, ...>
+        m = re.search(r"k_few(?:<|ILi)(\d)(?:, |ELi)(\d)", name)
+        if m:
+            base = "k_few (" + ("QKV", "gate/up", "O, down")[int(m.group(1))] + \
                 (", split A" if m.group(2) == "2" else "") + ")"
     return base
 
