@@ -247,9 +247,10 @@ __device__ __forceinline__ void block_topk(const float (*sims)[RT], int g0, int 
   }
 }
 
-// Scan of the bank: block `list` of nlists scores an even share of the
+// Scan of the bank: block (list, y) scores an even share (of nlists) of the
 // documents, at most 256 at a time, against up to RG KG keyframes, as a
-// [documents x D] . [D x 16 KG] product in fp32 (v_mfma_f32_16x16x4_f32).
+// [documents x D] . [D x 16 KG] product in fp32 (v_mfma_f32_16x16x4_f32), and
+// takes the keyframe groups y, y + gridDim.y, ... in turn.
 // Eight waves; of a batch's 16-document tiles wave w owns tiles w and w + 8.
 // Per 16 dimensions lane l loads 4 consecutive values of document (l % 16) of
 // each tile (16 rows x 64 contiguous bytes per load) and the matching 4
@@ -280,12 +281,15 @@ __global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
   __shared__ float qn[RG * KG];
   __shared__ float dn[RT];
   __shared__ float sims[RG * KG][RT];
-  const int nk = *n_keys, list = blockIdx.x;
+  const int nk = *n_keys, list = blockIdx.x, ny = gridDim.y;
+  // Groups of 16 if every one of them has a block of its own (two passes of
+  // half the lists side by side), otherwise 16 KG keyframes per pass.
+  const int rows = KG == 1 || nk <= RG * ny ? RG : RG * KG, first = blockIdx.y * rows;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const int QS = (D + 15) / 16 * 16 + 4, nfull = D / 16;
   const int sub = 4 * (lane >> 4);
   // n_sel counts finished keyframes in the merge (the next launch).
-  if (list == 0 && t == 0) *n_sel = 0;
+  if (list == 0 && first == 0 && t == 0) *n_sel = 0;
   const int b0 = (int)((long)ND * list / nlists), b1 = (int)((long)ND * (list + 1) / nlists);
   const int nb = (b1 - b0 + RT - 1) / RT;  // batches (at least one: nlists <= ND)
   const float *dp[NG];
@@ -308,16 +312,16 @@ __global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
       if (second) v[u][1] = *reinterpret_cast<const f32x4u *>(dp[1] + cc);
     }
   };
-  for (int g0 = 0; g0 < nk; g0 += RG * KG) {
-    const int ng = min(RG * KG, nk - g0);
+  for (int g0 = first; g0 < nk; g0 += rows * ny) {
+    const int ng = min(rows, nk - g0);
     const bool two = KG == 2 && ng > RG;  // the second column group is in use
     f32x4 va[4][NG], vb[4][NG];
 #pragma unroll
     for (int u = 0; u < 4; ++u) va[u][1] = vb[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     batch(0);
     if (nfull > 0) load(0, va);
-    if (g0 > 0) __syncthreads();  // the previous group's lists are done
-    for (int r = w; r < RG * KG; r += RM_T / 64) {  // a wave per row; rows past ng: zeros
+    if (g0 > first) __syncthreads();  // the previous group's lists are done
+    for (int r = w; r < rows; r += RM_T / 64) {  // a wave per row; rows past ng: zeros
       const float *src = frame_emb + (long)key_idx[g0 + min(r, ng - 1)] * D;
       float s = 0.f;
       for (int c = lane; c < QS; c += 64) {
@@ -560,21 +564,26 @@ hipError_t launch_retrieve(const float *frame_emb, const int32_t *key_idx, const
                            int32_t *top_idx, float *top_sim, int32_t *sel_idx, float *sel_sim,
                            int32_t *n_sel, hipStream_t s) {
   key_t64 *part = static_cast<key_t64 *>(ws);
-  // 32 keyframes per pass over the bank if there may be more than 16 and their
-  // rows (with 32 lists of similarities) fit the 160 KB of LDS. A list per
-  // block, as many blocks as the CUs hold at once (and lists as the workspace).
+  // Up to 32 keyframes per pass over the bank if there may be more than 16 and
+  // their rows (with 32 lists of similarities) fit the 160 KB of LDS. A list per
+  // block of documents, as many as the CUs hold blocks at once (and lists as the
+  // workspace); what a small bank leaves of them takes further groups of
+  // keyframes. (One block per list took the groups of a small bank in turn: 200
+  // keyframes against 156 and 5000 documents of 768 288 and 315 us, now 38 and
+  // 69; a grid sized for every frame being a keyframe 55 and 81 us.)
   const size_t qrow = ((size_t)(D + 15) / 16 * 16 + 4) * sizeof(float);
   const bool wide = NF > RG && 2 * RG * (qrow + RT * sizeof(float)) <= (size_t)150 << 10;
   const int rows = wide ? 2 * RG : RG;
   const size_t lds = rows * (qrow + RT * sizeof(float)) + 2048;
   const int per_cu = (int)std::min<size_t>(2, std::max<size_t>(1, (size_t)(160 << 10) / lds));
   const int nlists = std::min((ND + RT - 1) / RT, 256 * per_cu);
+  const dim3 grid(nlists, std::min((NF + RG - 1) / RG, 256 * per_cu / nlists));
   if (wide)
-    k_retrieve_scan<2><<<nlists, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D,
-                                                         k, nlists, part, n_sel);
+    k_retrieve_scan<2><<<grid, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D, k,
+                                                       nlists, part, n_sel);
   else
-    k_retrieve_scan<1><<<nlists, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D,
-                                                         k, nlists, part, n_sel);
+    k_retrieve_scan<1><<<grid, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D, k,
+                                                       nlists, part, n_sel);
   k_retrieve_merge<<<NF, MERGE_T, 0, s>>>(part, n_keys, nlists, k, K, top_idx, top_sim, sel_idx,
                                           sel_sim, n_sel);
   return hipGetLastError();

@@ -1,9 +1,9 @@
 """Edges of the dispatches of the retrieval stage and of the entity alignment,
 against float64 or integer references computed here: parts of a frame, frames
 that start at every byte alignment, more than 64 frames per keyframe thread,
-one, two and three keyframe groups per scan of the bank (16 or 32 keyframes
-each), widths with a partial last piece and unaligned rows, several batches
-per block, and both forms of the alignment on either side of their line.
+groups of 16 and of 32 keyframes, side by side and in turn, widths with a
+partial last piece and unaligned rows, several batches of documents per block,
+and both forms of the alignment on either side of their line.
 
 Bars: counts and indices exact; similarities within 1e-6 (float32 sums of at
 most 900 terms of a unit vector product: n eps / 2 is 5e-5 in the worst case,
@@ -49,17 +49,42 @@ def test_keyframes_against_counts(nf, h, w):
     np.testing.assert_array_equal(key_idx.cpu().numpy()[:len(keys)], keys)
 
 
-@pytest.mark.parametrize("nf,nk,nd,dim,k,K", [
-    (12, 12, 513, 48, 2, 3),       # one group of 16, aligned
-    (40, 16, 300, 35, 3, 5),       # unaligned rows, a partial piece
-    (40, 17, 300, 36, 16, 64),     # the second 16 of a group of 32
-    (70, 70, 2000, 100, 5, 40),    # three groups of 32
-    (40, 40, 700, 900, 3, 9),      # rows too long for 32: three groups of 16
-    (20, 20, 70001, 20, 4, 8),     # two batches per block
-    (300, 200, 90, 13, 16, 64),    # more than 1024 entries to select from
-    (3, 1, 1, 1, 1, 1),
+def _scan_plan(nf, nk, nd, dim):
+    """The bank scan's launch: keyframes per pass, passes of the busiest block,
+    batches (at most 256 documents each) of the largest share."""
+    row = ((dim + 15) // 16 * 16 + 4) * 4
+    wide = nf > 16 and 32 * (row + 1024) <= 150 << 10
+    rows = 32 if wide else 16
+    blocks = 256 * min(2, max(1, (160 << 10) // (rows * (row + 1024) + 2048)))
+    nlists = min((nd + 255) // 256, blocks)
+    ny = min((nf + 15) // 16, blocks // nlists)
+    if nk <= 16 * ny:
+        rows = 16
+    groups = (nk + rows - 1) // rows
+    return rows, (groups + ny - 1) // ny, (-(-nd // nlists) + 255) // 256
+
+
+# `plan`: keyframes per pass, passes, batches.
+@pytest.mark.parametrize("nf,nk,nd,dim,k,K,plan", [
+    (12, 12, 513, 48, 2, 3, (16, 1, 1)),       # one group of 16, aligned
+    (40, 16, 300, 35, 3, 5, (16, 1, 1)),       # unaligned rows, a partial piece
+    (40, 17, 300, 36, 16, 64, (16, 1, 1)),     # two groups side by side
+    (70, 70, 2000, 100, 5, 40, (16, 1, 1)),    # five
+    (40, 40, 700, 900, 3, 9, (16, 1, 1)),      # one block per CU
+    (40, 40, 66000, 900, 3, 9, (32, 2, 2)),    # ... and more documents than one batch each
+    (20, 20, 70001, 20, 4, 8, (32, 1, 1)),     # the second 16 of a group of 32
+    (70, 70, 70001, 20, 4, 8, (32, 3, 1)),     # three groups of 32 in turn
+    (300, 200, 90, 13, 16, 64, (16, 1, 1)),    # more than 1024 entries to select from
+    (300, 300, 20000, 13, 2, 9, (32, 2, 1)),   # groups of 32 side by side and in turn
+    (40, 40, 43600, 944, 3, 9, (16, 2, 1)),    # rows too long for 32: groups of 16 in turn
+    (3, 1, 1, 1, 1, 1, (16, 1, 1)),
+    # Several batches, the wave's second tile in use in every other one (128 and
+    # 129 documents), its stored list merged, in a second group as well.
+    (40, 40, 512 * 257, 20, 4, 8, (32, 2, 2)),
+    (16, 16, 512 * 257, 20, 4, 8, (16, 1, 2)),
 ])
-def test_retrieve_groups(nf, nk, nd, dim, k, K):
+def test_retrieve_groups(nf, nk, nd, dim, k, K, plan):
+    assert _scan_plan(nf, nk, nd, dim) == plan
     torch = _torch()
     from paper_2601_01513_amd.binding import Retriever
     g = torch.Generator(device="cuda")
@@ -90,6 +115,31 @@ def test_retrieve_groups(nf, nk, nd, dim, k, K):
     assert sel_idx.cpu().numpy()[:n].tolist() == [d for d, _ in want]
     np.testing.assert_array_equal(sel_sim.cpu().numpy()[:n],
                                   np.array([v for _, v in want], dtype=np.float32))
+
+
+def test_small_bank_takes_many_keyframes_side_by_side():
+    """200 keyframes against a question's own 156 documents: about 1.1 times the
+    time of 16 (38 and 35 us); their groups one after the other took 8 times."""
+    torch = _torch()
+    from paper_2601_01513_amd.binding import Retriever
+    femb, docs = torch.randn((200, 768), device="cuda"), torch.randn((156, 768), device="cuda")
+
+    def us(nk):
+        r = Retriever(200, 1, 1, 156, 768, 3, 5)
+        r.key_idx.copy_(torch.arange(200, device="cuda"))
+        r.n_keys.fill_(nk)
+        runs = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                r.retrieve(femb, docs)
+            b.record()
+            torch.cuda.synchronize()
+            runs.append(a.elapsed_time(b) * 50.0)
+        return min(runs)
+
+    assert us(200) < 2.5 * us(16)
 
 
 @pytest.mark.parametrize("strategy", ["two_stage", "addition", "invert"])
