@@ -12,6 +12,8 @@
 // takes component j of both operands, i.e. contraction index 4 (l / 16) + j in
 // lane group l / 16, the same index for both.
 // Result layout: lane l, register r: row 4 (l / 16) + r, column l % 16.
+#include <algorithm>
+
 #include "common.h"
 
 namespace vsr {
@@ -58,7 +60,7 @@ enum { EPI_QKV, EPI_RESIDUAL, EPI_SWIGLU, EPI_LSE, EPI_ARGMAX };
 struct F32Gemm {
   const float *A, *W;
   int rows, K, n;  // n: rotary pairs (QKV), F (SwiGLU), or rows of W
-  int nrt;         // row tiles: block b is row tile b % nrt, column tile b / nrt
+  int nrt, ct0;    // row tiles: block b is row tile b % nrt, column tile ct0 + b / nrt
   const float *g;
   float eps;
   const int32_t *row_lo;  // not NULL: row t is h_last if row_lo[t] == t, else A[t - 1]
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(256) void k_f32_gemm(F32Gemm a) {
   __shared__ float red[4][MG * NG][256];
   __shared__ float ssq[4][MG * 16];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, c16 = lane & 15, sub = 4 * (lane >> 4);
-  const int ct = blockIdx.x / a.nrt;
+  const int ct = a.ct0 + blockIdx.x / a.nrt;
   const int m0 = (blockIdx.x % a.nrt) * 16 * MG, u0 = ct * COLS;
   const int K = a.K;
   const float *ap[MG], *wp[NG];
@@ -291,17 +293,23 @@ template <int EPI, int MG, int NG, bool NORM>
 hipError_t launch_tile(F32Gemm a, hipStream_t s) {
   constexpr int COLS = EPI == EPI_QKV || EPI == EPI_SWIGLU ? 8 * NG : 16 * NG;
   a.nrt = (a.rows + 16 * MG - 1) / (16 * MG);
-  const long blocks = (long)a.nrt * ((a.n + COLS - 1) / COLS);
-  if (blocks > (1L << 23)) return hipErrorInvalidValue;  // threads of a launch: below 2^32
-  const unsigned grid = (unsigned)blocks;
+  const int nct = (a.n + COLS - 1) / COLS;
+  // The threads of a launch stay below 2^32 (113k scored rows of a 152k
+  // vocabulary reach it): further column tiles take further launches.
+  const int per = std::max(1, (1 << 23) / a.nrt);
   // 16-byte loads need aligned rows; other widths and bases load by element.
   const bool fast = a.K % 16 == 0 && aligned16(a.A) && aligned16(a.W) &&
                     (!NORM || aligned16(a.g)) && (!a.row_lo || aligned16(a.h_last));
-  if (fast)
-    k_f32_gemm<EPI, MG, NG, NORM, true><<<grid, 256, 0, s>>>(a);
-  else
-    k_f32_gemm<EPI, MG, NG, NORM, false><<<grid, 256, 0, s>>>(a);
-  return hipGetLastError();
+  for (a.ct0 = 0; a.ct0 < nct; a.ct0 += per) {
+    const unsigned grid = (unsigned)a.nrt * std::min(per, nct - a.ct0);
+    if (fast)
+      k_f32_gemm<EPI, MG, NG, NORM, true><<<grid, 256, 0, s>>>(a);
+    else
+      k_f32_gemm<EPI, MG, NG, NORM, false><<<grid, 256, 0, s>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Tile rule: 32 rows x 64 weight rows (16 FLOP per operand byte) once that

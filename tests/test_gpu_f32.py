@@ -96,3 +96,27 @@ def test_f32_candidates_do_not_see_each_others_nan():
     np.testing.assert_allclose(got[[0, 2]], clean[[0, 2]], rtol=0, atol=1e-5)
     np.testing.assert_allclose(got[1, :3], clean[1, :3], rtol=0, atol=1e-5)
     assert np.isnan(got[1, 4:]).all()
+
+
+def test_f32_head_past_one_launch():
+    """131072 scored rows of a 140000-entry vocabulary: 9 million blocks of the
+    LM head, more than one launch takes. A candidate's log-probs do not depend
+    on how many others are scored with it."""
+    torch = _torch()
+    import dataclasses
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = _cfg(32, 2, 2, 16, 32, 140000, 8, 0, 256, 512)
+    small = dataclasses.replace(cfg, n_cands=2)
+    wl = W.make_workload(small, 3, device="cuda")
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    few = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    few[:, -1] = cfg.vocab - 1  # a target of the last column tile
+    many = few[torch.arange(256, device="cuda") % 2].contiguous()
+    v = Verifier(small, wl.weights, device="cuda")
+    v.prefill(None, ids)
+    ref = v.score(few, [512] * 2)[0]
+    v = Verifier(cfg, wl.weights, device="cuda")
+    v.prefill(None, ids)
+    got = v.score(many, [512] * 256)[0]
+    assert torch.isfinite(ref).all()
+    assert (got.view(128, 2, 512) - ref).abs().max().item() <= 1e-5
