@@ -39,11 +39,14 @@
 // remainder planes and the probabilities are split the same way; each product
 // takes three MFMAs (hi.hi + hi.lo + lo.hi), which leaves an error of the
 // order of fp32 rounding. The query remainders also sit in registers (all 256
-// of a wave at two waves per SIMD, no spills in the prefill). Blocks of 4 waves
-// on 128 rows, as the 128 KB of LDS would also allow, left each SIMD one wave,
-// whose softmax and LDS waits nothing covered, and staged every tile for half
-// the rows: prefill at 4096 / 16384 keys of the 7B shape 464 / 7106 us, now 347 /
-// 5469 us; candidates 148 / 1686, now 111 / 1191 us.
+// of a wave at two waves per SIMD; the candidate pass spills three, the others
+// none). Blocks of 4 waves on 128 rows leave each SIMD one wave, whose softmax
+// and LDS waits nothing covers, and stage every tile for half the rows: prefill
+// at 4096 / 16384 keys of the 7B shape 464 / 7106 us, on 8 waves 347 / 5469 us;
+// candidates 148 / 1686 and 111 / 1191 us. Passes of few blocks, bound by a block's
+// latency, keep the 4 waves (launch_precise). With split keys a block's chunks
+// follow its own rows' first and last token, so the two shapes sum a query's keys
+// in chunks of other bounds: equal to fp32 rounding, not bit for bit.
 #include <algorithm>
 
 #include "common.h"
@@ -57,14 +60,13 @@ constexpr int KT = 64;    // keys per tile
 constexpr int KCH = KT * 16;   // 16-byte chunks of a K tile  [64 keys][128 dims]
 constexpr int VCH = HD * 8;    // 16-byte chunks of a V^T tile [128 dims][64 keys]
 
-// Block shape of the fast (PREC = false), precise (PREC = true) and decode
-// (DEC: one wave, the draft pass's decode steps with at most 32 stacked query
-// rows per KV head, where a wider block would mostly compute padding rows)
-// variants. An LDS stage holds [K | V^T] tiles, precise: [K | V^T | K lo |
-// V^T lo].
-template <bool PREC, bool DEC = false>
+// Block shape of the fast (PREC = false) and precise (PREC = true) variants:
+// NW waves, usually 8; one wave in the draft pass's decode steps with at most
+// 32 stacked query rows per KV head, where a wider block would mostly compute
+// padding rows; four in precise passes of few blocks (launch_precise). An LDS
+// stage holds [K | V^T] tiles, precise: [K | V^T | K lo | V^T lo].
+template <bool PREC, int NW = 8>
 struct Shape {
-  static constexpr int NW = DEC ? 1 : 8;   // waves per block
   static constexpr int NT = NW * 64;
   static constexpr int QT = NW * 32;       // stacked query rows per block
   static constexpr int STAGE = (PREC ? 2 : 1) * (KCH + VCH);
@@ -136,9 +138,8 @@ __device__ __forceinline__ void load_kv(const f16 *k, const f16 *vt, int npos, i
   }
 }
 
-template <bool PREC, bool DEC>
+template <bool PREC, int NW>
 __device__ __forceinline__ void load_tile(const Seg &sg, int kb, u32x4 *stage) {
-  constexpr int NW = Shape<PREC, DEC>::NW;
   load_kv<NW>(sg.k, sg.vt, sg.npos, kb, stage);
   if constexpr (PREC) load_kv<NW>(sg.k_lo, sg.vt_lo, sg.npos, kb, stage + KCH + VCH);
 }
@@ -392,12 +393,12 @@ __device__ __forceinline__ bool tile_clear(const Seg &sg, int kb) {
   return sg.mode == SEG_ALL;
 }
 
-template <bool PREC, bool DEC>
+template <bool PREC, int NW>
 __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
                                              float scale_log2) {
-  constexpr int STAGE = Shape<PREC, DEC>::STAGE;
+  constexpr int STAGE = Shape<PREC, NW>::STAGE;
   if (sg.kend <= sg.kbeg) return;
-  load_tile<PREC, DEC>(sg, sg.kbeg, lds);
+  load_tile<PREC, NW>(sg, sg.kbeg, lds);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // The mask-free tiles come first (tile_clear holds for a prefix of the
@@ -409,7 +410,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
   int stage = 0;
   int kb = sg.kbeg;
   while (kb < sg.kend && tile_clear(sg, kb)) {
-    if (kb + KT < sg.kend) load_tile<PREC, DEC>(sg, kb + KT, lds + STAGE);
+    if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds + STAGE);
     tile_any<false, PREC>(sg, kb, lds, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -418,7 +419,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
       stage = 1;
       break;
     }
-    if (kb + KT < sg.kend) load_tile<PREC, DEC>(sg, kb + KT, lds);
+    if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds);
     tile_any<false, PREC>(sg, kb, lds + STAGE, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -426,7 +427,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
   }
   for (; kb < sg.kend; kb += KT) {
     u32x4 *cur = lds + stage * STAGE;
-    if (kb + KT < sg.kend) load_tile<PREC, DEC>(sg, kb + KT, lds + (stage ^ 1) * STAGE);
+    if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds + (stage ^ 1) * STAGE);
     tile_any<true, PREC>(sg, kb, cur, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -437,15 +438,15 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
 // Tiles v0 .. v1-1 of the concatenation [prefix tiles 0 .. pre_t-1 | branch
 // tiles from key bbeg on]: one pipeline for both sources (the tile's source
 // is chosen per tile), so that one set of load offsets is live.
-template <bool PREC, bool DEC>
+template <bool PREC, int NW>
 __device__ __forceinline__ void walk_concat(const Seg &sp, const Seg &sb, int pre_t, int bbeg,
                                             int v0, int v1, u32x4 *lds, Lane &L,
                                             float scale_log2) {
-  constexpr int STAGE = Shape<PREC, DEC>::STAGE;
+  constexpr int STAGE = Shape<PREC, NW>::STAGE;
   if (v1 <= v0) return;
   auto src = [&](int v) -> const Seg & { return v < pre_t ? sp : sb; };
   auto key0 = [&](int v) { return v < pre_t ? v * KT : bbeg + (v - pre_t) * KT; };
-  load_tile<PREC, DEC>(src(v0), key0(v0), lds);
+  load_tile<PREC, NW>(src(v0), key0(v0), lds);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // Mask-free tiles first (whole prefix tiles), then the masked ones (a
@@ -454,7 +455,7 @@ __device__ __forceinline__ void walk_concat(const Seg &sp, const Seg &sb, int pr
   int v = v0;
   for (; v < v1 && tile_clear(src(v), key0(v)); ++v) {
     u32x4 *cur = lds + stage * STAGE;
-    if (v + 1 < v1) load_tile<PREC, DEC>(src(v + 1), key0(v + 1), lds + (stage ^ 1) * STAGE);
+    if (v + 1 < v1) load_tile<PREC, NW>(src(v + 1), key0(v + 1), lds + (stage ^ 1) * STAGE);
     tile_any<false, PREC>(src(v), key0(v), cur, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -462,7 +463,7 @@ __device__ __forceinline__ void walk_concat(const Seg &sp, const Seg &sb, int pr
   }
   for (; v < v1; ++v) {
     u32x4 *cur = lds + stage * STAGE;
-    if (v + 1 < v1) load_tile<PREC, DEC>(src(v + 1), key0(v + 1), lds + (stage ^ 1) * STAGE);
+    if (v + 1 < v1) load_tile<PREC, NW>(src(v + 1), key0(v + 1), lds + (stage ^ 1) * STAGE);
     tile_any<true, PREC>(src(v), key0(v), cur, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -474,10 +475,10 @@ __device__ __forceinline__ void walk_concat(const Seg &sp, const Seg &sb, int pr
 // mode 1: candidate pass (chunk blockIdx.z of [prefix tiles | the
 //         candidates' own tiles]);
 // mode 2: draft pass (chunk blockIdx.z of the prefix + branch-cache tiles).
-template <int MODE, bool PREC, bool DEC = false>
-__global__ __launch_bounds__((Shape<PREC, DEC>::NT)) void k_attn(AttnArgs a) {
-  constexpr int QT = Shape<PREC, DEC>::QT;
-  __shared__ u32x4 lds[2 * Shape<PREC, DEC>::STAGE];
+template <int MODE, bool PREC, int NW = 8>
+__global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
+  constexpr int QT = Shape<PREC, NW>::QT;
+  __shared__ u32x4 lds[2 * Shape<PREC, NW>::STAGE];
   const int G = a.n_heads / a.n_kv, TG = (a.T - a.t0) * G;
   // Prefill: one block index over (query tile, KV head), tiles with more keys
   // first across all heads, so that the longest blocks start in the first
@@ -527,7 +528,7 @@ __global__ __launch_bounds__((Shape<PREC, DEC>::NT)) void k_attn(AttnArgs a) {
     const int ke = min(tok_last + 1, (int)((long)nt * (chunk + 1) / a.nchunks) * KT);
     Seg sg{a.k + koff, a.vt + koff, PREC ? a.k_lo + koff : nullptr,
            PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.T, kb, ke, SEG_CAUSAL, tok_first};
-    walk_segment<PREC, DEC>(sg, lds, L, scale_log2);
+    walk_segment<PREC, NW>(sg, lds, L, scale_log2);
   } else if (MODE == 1) {
     // Candidate pass: chunk `chunk` walks an even share of the block's tiles
     // [prefix tiles | branch tiles], the branch tiles running from the
@@ -543,13 +544,13 @@ __global__ __launch_bounds__((Shape<PREC, DEC>::NT)) void k_attn(AttnArgs a) {
     Seg sp{a.k + koff, a.vt + koff, PREC ? a.k_lo + koff : nullptr,
            PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.P, min(a.P, c0 * KT),
            min(a.P, min(c1, pre_t) * KT), SEG_ALL, tok_first};
-    walk_segment<PREC, DEC>(sp, lds, L, scale_log2);
+    walk_segment<PREC, NW>(sp, lds, L, scale_log2);
     if (c1 > pre_t) {
       const int b0 = max(c0, pre_t) - pre_t;
       Seg sb{a.bk + boff, a.bvt + boff, PREC ? a.bk_lo + boff : nullptr,
              PREC ? a.bvt_lo + boff : nullptr, a.bk_npos, a.T, lo + b0 * KT,
              min(tok_last + 1, lo + (c1 - pre_t) * KT), SEG_BRANCH, tok_first};
-      walk_segment<PREC, DEC>(sb, lds, L, scale_log2);
+      walk_segment<PREC, NW>(sb, lds, L, scale_log2);
     }
   } else {
     // Draft pass (cache positions given): one query tile may hold rows of
@@ -568,7 +569,7 @@ __global__ __launch_bounds__((Shape<PREC, DEC>::NT)) void k_attn(AttnArgs a) {
     const Seg sb{a.bk + boff, a.bvt + boff, PREC ? a.bk_lo + boff : nullptr,
                  PREC ? a.bvt_lo + boff : nullptr, a.bk_npos, a.bk_valid, 0, 0, SEG_BRANCH,
                  tok_first};
-    walk_concat<PREC, DEC>(sp, sb, pre_t, lo, c0, c1, lds, L, scale_log2);
+    walk_concat<PREC, NW>(sp, sb, pre_t, lo, c0, c1, lds, L, scale_log2);
   }
 
   L.l = sum_halves(L.l);
@@ -681,14 +682,34 @@ __global__ __launch_bounds__(64 * NW) void k_attn_merge(AttnArgs a) {
   }
 }
 
-template <int MODE, bool PREC, bool DEC = false>
+template <int MODE, bool PREC, int NW = 8>
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
-  using S = Shape<PREC, DEC>;
+  using S = Shape<PREC, NW>;
   const int G = a.n_heads / a.n_kv;
   const int nqt = ((a.T - a.t0) * G + S::QT - 1) / S::QT;
   const dim3 grid = MODE == 0 ? dim3(nqt * a.n_kv, 1, a.nchunks) : dim3(nqt, a.n_kv, a.nchunks);
-  k_attn<MODE, PREC, DEC><<<grid, S::NT, 0, s>>>(a);
+  k_attn<MODE, PREC, NW><<<grid, S::NT, 0, s>>>(a);
   return hipGetLastError();
+}
+
+// A block of a precise pass fills a CU's LDS with either shape. Four waves on 128
+// rows pay a tile's latencies on fewer of them: the better shape while a pass of
+// such blocks is a single round (candidates and drafts), or while a prefix has
+// fewer than 176 tiles of 256 rows (its blocks run in several short rounds:
+// their key chunks and the causal bound even out). Past the line the eight waves
+// cover each other's waits and stage a tile for twice the rows. Measured, four /
+// eight waves: candidates of the 7B shape, 512 rows at 256 / 2048 / 8192 keys (112 /
+// 448 / 448 blocks of four) 37/46, 89/69, 263/183 us, of the 3B's 256 rows at 2048
+// (256 blocks) 37/42; 24 decode rows at 8192 keys 23/26; prefixes of 512 / 1536 /
+// 2048 rows of the 7B shape (56 / 168 / 224 tiles) 40/41, 107/108, 141/137, of 512 /
+// 2048 rows of the 1.5B's (24 / 96) 32/36, 103/111.
+template <int MODE>
+hipError_t launch_precise(const AttnArgs &a, hipStream_t s) {
+  const int rows = (a.T - a.t0) * (a.n_heads / a.n_kv);
+  const auto blocks = [&](int qt) { return (long)((rows + qt - 1) / qt) * a.n_kv; };
+  const bool four = MODE == 0 ? blocks(Shape<true>::QT) < 176
+                              : blocks(Shape<true, 4>::QT) * a.nchunks <= 256;
+  return four ? launch_attn<MODE, true, 4>(a, s) : launch_attn<MODE, true>(a, s);
 }
 
 }  // namespace
@@ -707,7 +728,7 @@ hipError_t attn_prefill(const AttnArgs &a, bool precise, hipStream_t s) {
   if (a.nchunks < 1 || a.nchunks > 64 || (a.nchunks > 1 && a.t0 != 0))
     return hipErrorInvalidValue;
   if (precise && (!a.q_lo || !a.k_lo || !a.vt_lo)) return hipErrorInvalidValue;
-  return precise ? launch_attn<0, true>(a, s) : launch_attn<0, false>(a, s);
+  return precise ? launch_precise<0>(a, s) : launch_attn<0, false>(a, s);
 }
 
 hipError_t attn_cascade(const AttnArgs &a, bool precise, hipStream_t s) {
@@ -716,13 +737,13 @@ hipError_t attn_cascade(const AttnArgs &a, bool precise, hipStream_t s) {
     return hipErrorInvalidValue;
   if (a.q_pos) {  // draft pass
     if (a.bk_valid <= 0) return hipErrorInvalidValue;
-    if (precise) return launch_attn<2, true>(a, s);
+    if (precise) return launch_precise<2>(a, s);
     // Decode steps: all stacked query rows of a KV head in one wave.
-    if ((a.T - a.t0) * (a.n_heads / a.n_kv) <= Shape<false, true>::QT)
-      return launch_attn<2, false, true>(a, s);
+    if ((a.T - a.t0) * (a.n_heads / a.n_kv) <= Shape<false, 1>::QT)
+      return launch_attn<2, false, 1>(a, s);
     return launch_attn<2, false>(a, s);
   }
-  return precise ? launch_attn<1, true>(a, s) : launch_attn<1, false>(a, s);
+  return precise ? launch_precise<1>(a, s) : launch_attn<1, false>(a, s);
 }
 
 hipError_t attn_merge(const AttnArgs &a, hipStream_t s) {

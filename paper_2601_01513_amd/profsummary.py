@@ -38,7 +38,7 @@ def _short(name: str) -> str:
     elif "k_attnILi1" in name or "k_attn<1" in name:
         base = "k_attn<1> (cascade" + (", precise)" if precise else ")")
     elif "k_attnILi2" in name or "k_attn<2" in name:
-        dec = "k_attnILi2ELb0ELb1E" in name or "k_attn<2, false, true>" in name
+        dec = "k_attnILi2ELb0ELi1E" in name or "k_attn<2, false, 1>" in name
         base = "k_attn<2> (draft" + (", precise)" if precise else
                                      ", decode blocks)" if dec else ")")
     elif base == "k_skinny":
