@@ -1485,7 +1485,7 @@ size_t gemm_split_floats(int rows, int N, int K) {
   return (size_t)ln.ntail * ln.nsplit * kTileElems;
 }
 
-// Where the four-wave kernels run: bit 0 the gate/up projection, bit 1 the
+// Where the four-wave kernels run (plain activations): bit 0 the gate/up projection, bit 1 the
 // residual projections with K >= kFourWaveMinK, bit 2 those with smaller K,
 // bit 3 the LM head. Building with VSR_FOUR_WAVE=<mask> changes it (for
 // comparisons).
@@ -1497,11 +1497,25 @@ constexpr int kFourWave = 3 | 8;
 constexpr int kFourWaveMinK = 8192;
 
 // The four-wave kernels' conditions: fp16 weights, and 32-bit byte offsets
-// reaching every operand row. Split activations gain as plain ones do (a 32B
-// layer of 10240 rows with its FFN split: 1.4 ms less than on the 8-wave tile).
+// reaching every operand row.
 inline bool four_wave_ok(bool w_f16, int asplit, int rows, int nrows_w, int K) {
   return w_f16 && K % BK == 0 && (size_t)rows * K * asplit * 2 <= UINT32_MAX &&
          (size_t)nrows_w * K * 2 <= UINT32_MAX;
+}
+
+// Whether split activations (nk panels, hi then lo) gain on the four-wave tile.
+// A block of it costs about 22 us more than one of the eight-wave tile (its loop
+// starts again at the remainder half, and the gate/up form spills 68 registers
+// where the plain one spills 11) and gains 0.28 us per panel, with one row tile,
+// whose operand rows repeat, about 0.7: the line is the panels of the longest
+// block. Measured, eight / four waves: gate/up of 4608 rows 441/479 us at 1.5B
+// widths (48 panels), 705/740 at 3B (64), 2099/1990 at 7B (112); of 64 rows 45/50
+// (16), 70/62 (32), 186/147 (112); down of 1.5B at 64, 2048, 4096 rows 61/67 (35),
+// 127/140 (56), 271/263 (140); of 3B at 64 78/75 (43); of 7B at 64, 768, 1024 rows
+// 122/109 (74), 215/223 (98), 288/277 (148); O of 32B at 256, 2048 rows 56/68 (20),
+// 264/231 (160).
+inline bool four_wave_split(const Launch &ln, int nk, int rows, int few) {
+  return (ln.ndp > 0 ? nk : nk / ln.nsplit) >= (rows <= 256 ? few : 100);
 }
 
 // Launch of four-wave kernel `kern<AS>`.
@@ -1558,8 +1572,9 @@ hipError_t gemm_residual(const f16 *A, const void *W, bool w_f16, int rows, int 
   }
   const Launch ln = plan_launch((rows + TL::BM - 1) / TL::BM, (N + TL::BN - 1) / TL::BN, 8,
                                 K / BK * asplit);
-  const int fw = K * asplit >= kFourWaveMinK ? 2 : 4;
-  if ((kFourWave & fw) && four_wave_ok(w_f16, asplit, rows, N, K))
+  const bool fw = asplit == 2 ? four_wave_split(ln, K / BK * 2, rows, 40)
+                              : (kFourWave & (K >= kFourWaveMinK ? 2 : 4)) != 0;
+  if (fw && four_wave_ok(w_f16, asplit, rows, N, K))
     VSR_4W_LAUNCH(k_gemm_residual_4w, A, W16, rows, N, K, ln, x, part);
   else
     VSR_WLAUNCH(k_gemm_residual, ln.blocks(), A, W16, rows, N, K, asplit, ln, x, part);
@@ -1580,7 +1595,8 @@ hipError_t gemm_swiglu(const f16 *A, const void *W, bool w_f16, int rows, int F,
   const Launch ln = plan_launch(nm, (F + 127) / 128, (nm + ng - 1) / ng, K / BK * asplit);
   // The four-wave tile with the ordered K loop where it applies (same
   // tiles, same partial layout).
-  if ((kFourWave & 1) && four_wave_ok(w_f16, asplit, rows, 2 * F, K))
+  const bool fw = asplit == 2 ? four_wave_split(ln, K / BK * 2, rows, 32) : (kFourWave & 1) != 0;
+  if (fw && four_wave_ok(w_f16, asplit, rows, 2 * F, K))
     VSR_4W_LAUNCH(k_gemm_swiglu_4w, A, W16, rows, F, K, ln, h, part);
   else
     VSR_WLAUNCH(k_gemm_swiglu, ln.blocks(), A, W16, rows, F, K, asplit, ln, h, part);

@@ -81,17 +81,23 @@ def test_fp16_and_bf16_weight_storage_score_identically(cfg):
     assert res["bf16"][2] == res["f16"][2]
 
 
-@pytest.mark.parametrize("rows,ff", [(3, 320), (300, 4160), (513, 4224), (700, 1216)])
-def test_split_products_agree_between_the_weight_forms(rows, ff):
+# (rows of the prefix, d_model, d_ff): the split products' panels per block lie on
+# either side of the lines (gate/up 32 and down 40 at up to 256 rows, 100 past
+# them): down 39, 40; gate/up 31, 32; down 98, 104; whole-K gate/up blocks of 104.
+@pytest.mark.parametrize("rows,d,ff", [(3, 256, 320), (300, 256, 4160), (513, 256, 4224),
+                                       (700, 256, 1216), (150, 256, 10176), (150, 256, 10240),
+                                       (150, 8128, 64), (150, 8192, 64), (300, 256, 25280),
+                                       (300, 256, 26624), (400, 3328, 8256)])
+def test_split_products_agree_between_the_weight_forms(rows, d, ff):
     """Precise layers with a split feed-forward block: fp16 weights run their
-    split products on the four-wave tile (gate/up at every size, the down
-    product from 2 K = 8192 on), bf16 weights on the eight-wave one; the same
-    products in the same order, so the log-probs are bit for bit equal. Whole
-    and partial tiles, split-K tails of both halves."""
+    split products on the four-wave tile where a block walks enough panels, bf16
+    weights on the eight-wave one; the same products in the same order, so the
+    log-probs are bit for bit equal. Whole and partial tiles, split-K tails of
+    both halves."""
     torch = _torch()
     from paper_2601_01513_amd.binding import Verifier
     cfg = W.VerifierConfig(
-        name=f"split rows {rows} F{ff}", n_layers=2, d_model=256, n_heads=2, n_kv_heads=1,
+        name=f"split rows {rows} d{d} F{ff}", n_layers=2, d_model=d, n_heads=2, n_kv_heads=1,
         head_dim=128, d_ff=ff, vocab=500, rope_base=1e6, dtype=W.BF16, n_prefix=rows,
         n_visual=0, n_cands=3, cand_len=50)
     wl = W.make_workload(cfg, 1, device="cuda")
