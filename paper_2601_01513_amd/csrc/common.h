@@ -386,8 +386,9 @@ hipError_t few_swiglu(const float *x, const bf16 *g, float eps, int rows, int as
 hipError_t few_residual(const f16 *A, int rows, int asplit, const void *W, bool w_f16, int N,
                         int K, float *x, hipStream_t s);
 // LM head of few rows as gemm_lmhead, in skinny_lse_chunks(vocab) equal chunks
-// (0: not supported).
+// (0: not supported); the better form up to skinny_lse_rows(K) rows.
 int skinny_lse_chunks(int vocab);
+int skinny_lse_rows(int K);
 hipError_t skinny_lmhead(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
                          const int32_t *lm_tgt, float2 *part, float *tgt_logit, hipStream_t s);
 // dst[i] = fp16 of the bf16 src[i], the GEMMs' in-register conversion.

@@ -1638,11 +1638,15 @@ hipError_t gemm_lmhead(const f16 *A, const void *W, bool w_f16, int rows, int vo
   const int nm = lmhead_chunks(vocab), nn = (rows + TL::BN - 1) / TL::BN;
   const Launch ln{nm, nn, 1, nm * nn, 0, 1};
   // At most 128 tokens: half a token tile of padding costs more than the
-  // smaller tile's extra LDS reads (80 tokens, 1.5B head: 147 against 162 us).
-  if (rows <= 128) {
+  // smaller tile's extra LDS reads (80 tokens, 1.5B head: 147 against 162 us)
+  // where the four-wave tile does not run or has short K: with fp16 weights, 64
+  // rows, K 1536 / 2048 149 / 199 us against 158 / 206 on four waves, K 3072 / 3584 /
+  // 5120 269 / 305 / 443 against 264 / 300 / 414; they meet near K 2560.
+  const bool fw = (kFourWave & 8) && four_wave_ok(w_f16, 1, vocab, rows, K);
+  if (rows <= 128 && !(fw && K > 2560)) {
     typedef Tile<256, 128, 4, 2> TL;
     VSR_WLAUNCH(k_gemm_lmhead, ln.blocks(), A, W16, rows, vocab, K, ln, lm_tgt, part, tgt_logit);
-  } else if ((kFourWave & 8) && four_wave_ok(w_f16, 1, vocab, rows, K))
+  } else if (fw)
     k_gemm_lmhead_4w<<<ln.blocks(), 256, 0, s>>>(A, static_cast<const uint16_t *>(W), rows, vocab,
                                                    K, ln, lm_tgt, part, tgt_logit);
   else

@@ -671,6 +671,15 @@ int skinny_lse_chunks(int vocab) {
   return vocab % (2 * SK_ROWS) == 0 ? vocab / (2 * SK_ROWS) : skinny_lm_chunks(vocab);
 }
 
+// Each row costs the stream its loads and products, more the wider the rows,
+// and the merge twice the tiles' chunks; a tile of up to 128 rows costs the same
+// for all of them. Head and merge of a 152k vocabulary, us: they cross past 32
+// rows at K 2048 (183 against 195 at 32), at 19 / 26 / 25 / 20 rows for K 2560 / 3072 /
+// 3584 / 4096, at 15 / 17 for 5120 / 8192 with fp16 weights (24 rows of 5120: 430
+// against 401), and at 21 to 28 with bf16 ones, where the tiles cost more. One
+// line for both, so that they score alike.
+int skinny_lse_rows(int K) { return K <= 2048 ? 32 : K <= 4096 ? 24 : 16; }
+
 hipError_t skinny_lmargmax(const f16 *A, int rows, const void *W, bool w_f16, int vocab, int K,
                            float2 *part, hipStream_t s) {
   if (rows == 0) return hipSuccess;

@@ -685,7 +685,7 @@ int lm_head(vsr_ctx *c, int rows, int *chunks) {
   // over the weights; a 256-row tile spends its matrix work on padding. 16
   // rows of the 7B head kept in bf16 (1.09 GB): 390 -> 267 us.
   if constexpr (kMfma) {
-    if (rows <= kSkinnyMaxRows && skinny_lse_chunks(cf.vocab) > 0) {
+    if (rows <= skinny_lse_rows(cf.d_model) && skinny_lse_chunks(cf.vocab) > 0) {
       *chunks = skinny_lse_chunks(cf.vocab);
       STAGE(c, K_LMHEAD, "lm head",
             skinny_lmhead(lm_in, rows, c->lm_head, wf16, cf.vocab, cf.d_model, lm_tgt, lm_part,

@@ -44,6 +44,38 @@ def test_lm_head_of_few_rows(vocab, lens):
     assert int(out[0][2][0]) == am or abs(sc[0] - sc[1]) < 0.1
 
 
+@pytest.mark.parametrize("d, rows", [(2048, 32), (2048, 33), (2112, 24), (2112, 25), (2560, 25),
+                                     (2624, 25), (4096, 24), (4160, 16), (4160, 17), (4160, 128)])
+def test_lm_head_lines(d, rows):
+    """Both sides of the lines between the stream and the tiles (rows, by width)
+    and between the tiles of up to 128 rows (width 2560, fp16 weights): the weight
+    storages, which take different tiles, agree bit for bit."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2601_01513_amd.binding import Verifier
+    cfg = W.VerifierConfig(
+        name=f"head d{d} rows {rows}", n_layers=1, d_model=d, n_heads=1, n_kv_heads=1,
+        head_dim=128, d_ff=64, vocab=1088, rope_base=1e6, dtype=W.BF16, n_prefix=20, n_visual=4,
+        n_cands=2, cand_len=rows)
+    wl = W.make_workload(cfg, rows, device="cuda")
+    lens = np.asarray([rows - 1, 1], dtype=np.int32)
+    wl.cand_ids[1, 1:] = 0
+    wl.cand_ids[0, 0] = cfg.vocab - 1
+    ids = torch.tensor(wl.prefix_ids, dtype=torch.int32, device="cuda")
+    cids = torch.tensor(wl.cand_ids, dtype=torch.int32, device="cuda")
+    out = []
+    for storage in ("f16", "bf16"):
+        v = Verifier(cfg, wl.weights, device="cuda", gemm_weights=storage)
+        v.prefill(wl.visual, ids)
+        out.append(v.score(cids, lens)[0].cpu().numpy())
+    np.testing.assert_array_equal(out[0], out[1])
+    ref, _, _ = oracle.score_shared_prefix(cfg, W.host_weights(wl.weights),
+                                           W.to_host_f32(wl.visual), wl.prefix_ids,
+                                           wl.cand_ids, lens)
+    assert np.abs(out[0] - ref).max() <= 2e-2
+
+
 # (d_model, heads, d_ff): the loads a wave's lanes make per weight row and the
 # waves left without any: 4 pairs of K for 16 waves; a long down projection on
 # few outputs; more than 256 output groups in several steps.
