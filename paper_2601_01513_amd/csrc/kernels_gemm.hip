@@ -790,8 +790,10 @@ __global__ __launch_bounds__(256) void k_gemm_residual_4w(const f16 *__restrict_
                        x);
 }
 
-// Gate/up projection + SwiGLU on the four-wave tile (fp16 weights). A wave's 128 B rows are 64 gate + 64 up rows, as in the
-// 8-wave kernel, so block columns j and j + 2 pair up in one lane.
+// Gate/up projection + SwiGLU on the four-wave tile (fp16 weights). A wave's
+// 128 B rows are 64 gate + 64 up rows, as in the 8-wave kernel, so block columns
+// j and j + 2 pair up in one lane. (AS = 2 spills 69 registers around the loop,
+// AS = 1 12: what that costs a block is in four_wave_split's line.)
 template <int AS>
 __global__ __launch_bounds__(256) void k_gemm_swiglu_4w(const f16 *__restrict__ A,
                                                         const uint16_t *__restrict__ W, int rows,
@@ -1505,8 +1507,8 @@ inline bool four_wave_ok(bool w_f16, int asplit, int rows, int nrows_w, int K) {
 
 // Whether split activations (nk panels, hi then lo) gain on the four-wave tile.
 // A block of it costs about 22 us more than one of the eight-wave tile (its loop
-// starts again at the remainder half, and the gate/up form spills 68 registers
-// where the plain one spills 11) and gains 0.28 us per panel, with one row tile,
+// starts again at the remainder half, and the gate/up form spills 69 registers
+// where the plain one spills 12) and gains 0.28 us per panel, with one row tile,
 // whose operand rows repeat, about 0.7: the line is the panels of the longest
 // block. Measured, eight / four waves: gate/up of 4608 rows 441/479 us at 1.5B
 // widths (48 panels), 705/740 at 3B (64), 2099/1990 at 7B (112); of 64 rows 45/50
@@ -1519,13 +1521,13 @@ inline bool four_wave_split(const Launch &ln, int nk, int rows, int few) {
 }
 
 // Launch of four-wave kernel `kern<AS>`.
-#define VSR_4W_LAUNCH(kern, ...)                                                   \
-  do {                                                                            \
-    const uint16_t *W16 = static_cast<const uint16_t *>(W);                       \
-    if (asplit == 2)                                                              \
-      kern<2><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                            \
-    else                                                                          \
-      kern<1><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                            \
+#define VSR_4W_LAUNCH(kern, ...)                                                  \
+  do {                                                                           \
+    const uint16_t *W16 = static_cast<const uint16_t *>(W);                      \
+    if (asplit == 2)                                                             \
+      kern<2><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                           \
+    else                                                                         \
+      kern<1><<<ln.blocks(), 256, 0, s>>>(__VA_ARGS__);                           \
   } while (0)
 
 // Weight-format dispatch of a GEMM kernel launch.
@@ -1533,22 +1535,25 @@ inline bool four_wave_split(const Launch &ln, int nk, int rows, int few) {
   do {                                                                           \
     const uint16_t *W16 = static_cast<const uint16_t *>(W);                      \
     if (w_f16)                                                                   \
-      kern<TL, false><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                           \
+      kern<TL, false><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                  \
     else                                                                         \
-      kern<TL, true><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                            \
+      kern<TL, true><<<grid, TL::NW * 64, 0, s>>>(__VA_ARGS__);                   \
   } while (0)
 
 // Launch of the small-tile form, or an empty one where the 256 x 256 tiles are
 // the better form (`base`: us of a small launch beside its panels). A small tile
-// takes its panels at the rate one CU loads them, 0.62 us each (0.75 with bf16
-// weights), whatever the number of blocks up to one a CU; a split launch about
-// 12 us (two launches, the reduce's round trips), 1.2 us per panel of a block
-// and 0.085 us per block for its partial tile (256 KB written and read). The line
-// lies where both weight storages gain, as both take the same form and score
-// alike. Measured, split and reduce / small (us, fp16; bf16 weights): O of 1.5B
-// at 512 rows 22/16; 23/21, at 1024 24/18; 23/22, at 2048 34/20; 32/23, at 3072
-// (two rounds) 38/35; 36/42; O of 3B at 1024 35/23; 31/29; O of 7B at 640 43/37;
-// 39/45; QKV of 1.5B at 1024 28/24; 27/29, at 2048 38/27; 35/31.
+// takes 0.5 us per panel with fp16 weights and 0.7 with bf16 ones (32 KB of
+// operands), whatever the number of blocks up to one a CU; 5 (QKV: 14) + 0.8 nk
+// bounds the bf16 launches of up to 80 panels from above, and longer ones never
+// gain. A split launch takes about 12 us (two launches, the reduce's round trips),
+// 1.2 us per panel of a block and 0.085 us per block for its partial tile (256 KB
+// written and read). Both storages take the same form and score alike, so the
+// line lies where the slower one, bf16, still gains or is even. Measured with the
+// weights of several layers in turn (out of the caches), split and reduce / small
+// (us, fp16; bf16 weights): O of 1.5B at 512 rows (not taken) 22/22; 23/25, at 768
+// 25/22; 25/25, at 1024 28/22; 28/25, at 2048 38/23; 39/27; O of 3B at 1024 37/27;
+// 37/31; O of 7B at 640 (not taken) 46/41; 46/48; QKV of 1.5B at 1024 (not taken)
+// 33/31; 33/33, at 2048 42/33; 41/36.
 Launch small_tiles(int rows, int N, int K, int asplit, float base) {
   const int nm = (rows + 127) / 128, nn = (N + 127) / 128, nk = K / BK * asplit;
   const Launch big = plan_launch((rows + 255) / 256, (N + 255) / 256, 8, nk);
