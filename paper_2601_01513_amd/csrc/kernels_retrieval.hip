@@ -537,11 +537,18 @@ hipError_t launch_keyframes(const uint8_t *frames, int NF, int H, int W, float t
                             int32_t *hist, int32_t *inter, int32_t *key_idx, int32_t *n_keys,
                             hipStream_t s) {
   const long fb = (long)H * W * 3;
-  // One block per frame stores the frame's counts. Fewer than 128 frames leave
-  // half of the CUs idle: larger frames are then cut into parts of at least 32
-  // KB that add into zeroed counts, one more launch (4.5 us).
+  // One block per frame stores the frame's counts. A block counts about 26 GB/s,
+  // so some 190 of them reach what the chip counts: fewer frames are cut into
+  // parts (of at least 32 KB, up to two blocks a CU) that add into zeroed counts,
+  // where the time the idle CUs save, frame bytes x (190 - NF) / 190 / 26 GB/s, is
+  // above that of the extra launch, about 2 us, and a frame is above 64 KB (8
+  // frames of 120 x 160: 9.4 whole, 10.3 in parts). In two parts, past 170 frames,
+  // it gains nothing. Whole frames / parts, us: 130 frames of 336 x 336 22.2/20.8, of
+  // 480 x 854 55/43, of 1080 x 1920 243/177; 127 of 200 x 200 13.4/14.0, of 224 x 224
+  // 14.7/14.1; 175 of 480 x 854 56/57.
   int split = 1;
-  if (NF < 128 && fb > (64 << 10)) split = (int)std::min<long>((511 + NF) / NF, fb >> 15);
+  if (NF <= 170 && fb > (64 << 10) && fb * (190 - NF) > 9000000)
+    split = (int)std::max<long>(2, std::min<long>(512 / NF, fb >> 15));
   if (split == 1) {
     k_hist<false><<<NF, HIST_T, 0, s>>>(frames, fb, 1, hist);
   } else {

@@ -25,7 +25,8 @@ def _torch():
 
 
 @pytest.mark.parametrize("nf,h,w", [(3, 150, 161), (5, 256, 256), (2, 1, 30000), (127, 149, 148),
-                                    (130, 149, 149), (16, 7, 3), (1500, 2, 3), (65, 1, 1)])
+                                    (130, 149, 149), (16, 7, 3), (1500, 2, 3), (65, 1, 1),
+                                    (130, 224, 224), (170, 401, 401), (171, 401, 401)])
 def test_keyframes_against_counts(nf, h, w):
     torch = _torch()
     from paper_2601_01513_amd.binding import Retriever
