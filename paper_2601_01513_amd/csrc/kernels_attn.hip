@@ -44,9 +44,8 @@
 // and LDS waits nothing covers, and stage every tile for half the rows: prefill
 // at 4096 / 16384 keys of the 7B shape 464 / 7106 us, on 8 waves 347 / 5469 us;
 // candidates 148 / 1686 and 111 / 1191 us. Passes of few blocks, bound by a block's
-// latency, keep the 4 waves (launch_precise). With split keys a block's chunks
-// follow its own rows' first and last token, so the two shapes sum a query's keys
-// in chunks of other bounds: equal to fp32 rounding, not bit for bit.
+// latency, keep the 4 waves (launch_precise); results do not depend on the shape,
+// except that a draft pass's key chunks follow the rows of its blocks.
 #include <algorithm>
 
 #include "common.h"
@@ -393,11 +392,26 @@ __device__ __forceinline__ bool tile_clear(const Seg &sg, int kb) {
   return sg.mode == SEG_ALL;
 }
 
+// A run of keys [beg, end), beg a multiple of KT.
+struct Span {
+  int beg, end;
+};
+__device__ __forceinline__ Span span_union(Span a, Span b) {
+  if (a.beg >= a.end) return b;
+  if (b.beg >= b.end) return a;
+  return {min(a.beg, b.beg), max(a.end, b.end)};
+}
+
+// `mine`: the tiles of the walk that this wave takes part in (eight precise
+// waves: those of its half of the block's rows; otherwise all of them).
 template <bool PREC, int NW>
-__device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
+__device__ __forceinline__ void walk_segment(const Seg &sg, Span mine, u32x4 *lds, Lane &L,
                                              float scale_log2) {
   constexpr int STAGE = Shape<PREC, NW>::STAGE;
   if (sg.kend <= sg.kbeg) return;
+  const auto takes = [&](int kb) {
+    return !(PREC && NW == 8) || (kb >= mine.beg && kb < mine.end);
+  };
   load_tile<PREC, NW>(sg, sg.kbeg, lds);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -411,7 +425,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
   int kb = sg.kbeg;
   while (kb < sg.kend && tile_clear(sg, kb)) {
     if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds + STAGE);
-    tile_any<false, PREC>(sg, kb, lds, L, scale_log2);
+    if (takes(kb)) tile_any<false, PREC>(sg, kb, lds, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     kb += KT;
@@ -420,7 +434,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
       break;
     }
     if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds);
-    tile_any<false, PREC>(sg, kb, lds + STAGE, L, scale_log2);
+    if (takes(kb)) tile_any<false, PREC>(sg, kb, lds + STAGE, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     kb += KT;
@@ -428,7 +442,7 @@ __device__ __forceinline__ void walk_segment(const Seg &sg, u32x4 *lds, Lane &L,
   for (; kb < sg.kend; kb += KT) {
     u32x4 *cur = lds + stage * STAGE;
     if (kb + KT < sg.kend) load_tile<PREC, NW>(sg, kb + KT, lds + (stage ^ 1) * STAGE);
-    tile_any<true, PREC>(sg, kb, cur, L, scale_log2);
+    if (takes(kb)) tile_any<true, PREC>(sg, kb, cur, L, scale_log2);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     stage ^= 1;
@@ -515,43 +529,68 @@ __global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
   }
   const float scale_log2 = 1.4426950408889634f * rsqrtf((float)HD);
   L.thr = 8.f / scale_log2;
-  const int tok_first = a.t0 + q0 / G;
-  const int tok_last = a.t0 + min(q0 + QT - 1, TG - 1) / G;
-
   const int chunk = blockIdx.z;
   const long koff = (long)kvh * a.kv_npos * HD, boff = (long)kvh * a.bk_npos * HD;
+  // With split keys the chunks follow the rows' first and last token. Eight
+  // precise waves take them per half of their rows, as two blocks of four waves
+  // do, so that both shapes sum a query's keys in the same chunks.
+  constexpr int HALVES = PREC && NW == 8 && MODE < 2 ? 2 : 1;
+  const int half = HALVES == 2 ? __builtin_amdgcn_readfirstlane(w >> 2) : 0;
+  const auto first_tok = [&](int h) {
+    const int r = q0 + h * (QT / HALVES);
+    return a.t0 + (r < TG ? r : q0) / G;  // (a half past the rows walks as the first)
+  };
+  const auto last_tok = [&](int h) {
+    const int r = q0 + h * (QT / HALVES);
+    return a.t0 + min((r < TG ? r : q0) + QT / HALVES - 1, TG - 1) / G;
+  };
+  const int tok_first = a.t0 + q0 / G;
   if (MODE == 0) {
-    // Causal keys 0 .. tok_last; with nchunks > 1 (few blocks on the chip)
-    // chunk `chunk` takes an even share of the block's key tiles.
-    const int nt = (tok_last + KT) / KT;
-    const int kb = (int)((long)nt * chunk / a.nchunks) * KT;
-    const int ke = min(tok_last + 1, (int)((long)nt * (chunk + 1) / a.nchunks) * KT);
+    // Causal keys 0 .. the last token; with nchunks > 1 (few blocks on the chip)
+    // chunk `chunk` takes an even share of the key tiles.
+    const auto span = [&](int h) {
+      const int last = last_tok(h), nt = (last + KT) / KT;
+      return Span{(int)((long)nt * chunk / a.nchunks) * KT,
+                  min(last + 1, (int)((long)nt * (chunk + 1) / a.nchunks) * KT)};
+    };
+    const Span all = HALVES == 2 ? span_union(span(0), span(1)) : span(0);
     Seg sg{a.k + koff, a.vt + koff, PREC ? a.k_lo + koff : nullptr,
-           PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.T, kb, ke, SEG_CAUSAL, tok_first};
-    walk_segment<PREC, NW>(sg, lds, L, scale_log2);
+           PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.T, all.beg, all.end, SEG_CAUSAL,
+           tok_first};
+    walk_segment<PREC, NW>(sg, span(half), lds, L, scale_log2);
   } else if (MODE == 1) {
-    // Candidate pass: chunk `chunk` walks an even share of the block's tiles
-    // [prefix tiles | branch tiles], the branch tiles running from the
-    // block's first query's segment start to its last query (both
-    // non-decreasing in token order). (With the branch tiles all on the last
-    // chunk on top of an even share of the prefix, that chunk bounded the
-    // launch.)
+    // Candidate pass: chunk `chunk` walks an even share of the tiles [prefix
+    // tiles | branch tiles], the branch tiles running from the first query's
+    // segment start to the last query (both non-decreasing in token order).
+    // (With the branch tiles all on the last chunk on top of an even share of the
+    // prefix, that chunk bounded the launch.)
     const int pre_t = (a.P + KT - 1) / KT;
-    const int lo = a.row_lo[tok_first] & ~(KT - 1);
-    const int tot = pre_t + (tok_last + 1 - lo + KT - 1) / KT;
-    const int c0 = (int)((long)tot * chunk / a.nchunks);
-    const int c1 = (int)((long)tot * (chunk + 1) / a.nchunks);
-    Seg sp{a.k + koff, a.vt + koff, PREC ? a.k_lo + koff : nullptr,
-           PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.P, min(a.P, c0 * KT),
-           min(a.P, min(c1, pre_t) * KT), SEG_ALL, tok_first};
-    walk_segment<PREC, NW>(sp, lds, L, scale_log2);
-    if (c1 > pre_t) {
-      const int b0 = max(c0, pre_t) - pre_t;
-      Seg sb{a.bk + boff, a.bvt + boff, PREC ? a.bk_lo + boff : nullptr,
-             PREC ? a.bvt_lo + boff : nullptr, a.bk_npos, a.T, lo + b0 * KT,
-             min(tok_last + 1, lo + (c1 - pre_t) * KT), SEG_BRANCH, tok_first};
-      walk_segment<PREC, NW>(sb, lds, L, scale_log2);
+    const auto spans = [&](int h, Span &pre, Span &br) {
+      const int last = last_tok(h), lo = a.row_lo[first_tok(h)] & ~(KT - 1);
+      const int tot = pre_t + (last + 1 - lo + KT - 1) / KT;
+      const int c0 = (int)((long)tot * chunk / a.nchunks);
+      const int c1 = (int)((long)tot * (chunk + 1) / a.nchunks);
+      pre = {min(a.P, c0 * KT), min(a.P, min(c1, pre_t) * KT)};
+      br = {lo + (max(c0, pre_t) - pre_t) * KT,
+            c1 > pre_t ? min(last + 1, lo + (c1 - pre_t) * KT) : 0};
+    };
+    Span pre, br, my_pre, my_br;
+    spans(half, my_pre, my_br);
+    pre = my_pre;
+    br = my_br;
+    if constexpr (HALVES == 2) {
+      Span other_pre, other_br;
+      spans(half ^ 1, other_pre, other_br);
+      pre = span_union(pre, other_pre);
+      br = span_union(br, other_br);
     }
+    Seg sp{a.k + koff, a.vt + koff, PREC ? a.k_lo + koff : nullptr,
+           PREC ? a.vt_lo + koff : nullptr, a.kv_npos, a.P, pre.beg, pre.end, SEG_ALL, tok_first};
+    walk_segment<PREC, NW>(sp, my_pre, lds, L, scale_log2);
+    Seg sb{a.bk + boff, a.bvt + boff, PREC ? a.bk_lo + boff : nullptr,
+           PREC ? a.bvt_lo + boff : nullptr, a.bk_npos, a.T, br.beg, br.end, SEG_BRANCH,
+           tok_first};
+    walk_segment<PREC, NW>(sb, my_br, lds, L, scale_log2);
   } else {
     // Draft pass (cache positions given): one query tile may hold rows of
     // several branches, whose cache segments lie between the block's first
@@ -560,7 +599,7 @@ __global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
     // branch tiles].
     const int pre_t = (a.P + KT - 1) / KT;
     const int lo = a.row_lo[tok_first] & ~(KT - 1);
-    const int hi = a.q_pos[tok_last];
+    const int hi = a.q_pos[last_tok(0)];
     const int tot = pre_t + (hi - lo) / KT + 1;
     const int c0 = (int)((long)tot * chunk / a.nchunks);
     const int c1 = (int)((long)tot * (chunk + 1) / a.nchunks);
