@@ -175,6 +175,7 @@ __global__ __launch_bounds__(1024) void k_keyframes(const int32_t *hist, int NF,
 
 constexpr int RG = 16;       // keyframes per column group of the bank scan
 constexpr int RT = 256;      // documents a block scores at a time
+constexpr int kMaxLists = 512;  // lists per keyframe: two blocks a CU
 
 // A ranked candidate as one unsigned 64-bit key: the similarity's
 // order-preserving bits above the complement of the document index, so a
@@ -436,10 +437,9 @@ __device__ __forceinline__ T get_agent(const T *p) {
 // Block r < n_keys: the top-k of keyframe r over every block's top-k, then, in
 // the block that finishes last, T* = the K best documents of the union of the
 // top-k lists, a document scored by the best similarity it was retrieved with
-// (Eq. 3). Each wave takes the top-k of its own share of the candidates (the
-// first MERGE_PER per thread in registers; a larger bank's further ones are
-// re-read on each pass) without block barriers, then wave 0 merges the 16
-// lists. The finished keyframes are counted in n_sel, which the scan zeroed
+// (Eq. 3). Each wave takes the top-k of its own share of the candidates (at most
+// MERGE_PER per thread, in registers) without block barriers, then wave 0 merges
+// the 16 lists. The finished keyframes are counted in n_sel, which the scan zeroed
 // and which gets its value at the end. The lists are stored and loaded at
 // agent scope, and a block counts itself once its stores are acknowledged (an
 // agent-scope release would write back the whole L2: 13.7 us for 6 candidates
@@ -447,6 +447,7 @@ __device__ __forceinline__ T get_agent(const T *p) {
 // for 12 keyframes over 100k documents, now 7.7 us.
 constexpr int MERGE_T = 1024;
 constexpr int MERGE_PER = 8;
+static_assert(kMaxLists * 16 <= MERGE_T * MERGE_PER, "k <= 16 candidates of every list");
 __global__ __launch_bounds__(MERGE_T) void k_retrieve_merge(const key_t64 *part,
                                                             const int32_t *n_keys, int nlists,
                                                             int k, int K, int32_t *top_idx,
@@ -467,7 +468,6 @@ __global__ __launch_bounds__(MERGE_T) void k_retrieve_merge(const key_t64 *part,
     key_t64 best = 0ull;
 #pragma unroll
     for (int e = 0; e < MERGE_PER; ++e) best = max_below(best, c[e], last);
-    for (int j = t + MERGE_PER * MERGE_T; j < n; j += MERGE_T) best = max_below(best, p[j], last);
     last = wave_best(best);
     if (lane == 0) wl[16 * q + w] = last;
     // (0: the wave's candidates are used up, the remaining passes find none)
@@ -561,6 +561,9 @@ hipError_t launch_keyframes(const uint8_t *frames, int NF, int H, int W, float t
   return hipGetLastError();
 }
 
+// One list per 256 documents and keyframe: what callers size their buffers by, and
+// the static scratch refuses calls by. Banks of more than kMaxLists x 256 documents
+// use kMaxLists of them.
 size_t retrieve_workspace_bytes(int NF, int ND, int k) {
   const size_t nchunks = ((size_t)ND + RT - 1) / RT;
   return (size_t)NF * nchunks * (size_t)k * sizeof(key_t64);
@@ -583,8 +586,8 @@ hipError_t launch_retrieve(const float *frame_emb, const int32_t *key_idx, const
   const int rows = wide ? 2 * RG : RG;
   const size_t lds = rows * (qrow + RT * sizeof(float)) + 2048;
   const int per_cu = (int)std::min<size_t>(2, std::max<size_t>(1, (size_t)(160 << 10) / lds));
-  const int nlists = std::min((ND + RT - 1) / RT, 256 * per_cu);
-  const dim3 grid(nlists, std::min((NF + RG - 1) / RG, 256 * per_cu / nlists));
+  const int blocks = kMaxLists / 2 * per_cu, nlists = std::min((ND + RT - 1) / RT, blocks);
+  const dim3 grid(nlists, std::min((NF + RG - 1) / RG, blocks / nlists));
   if (wide)
     k_retrieve_scan<2><<<grid, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D, k,
                                                        nlists, part, n_sel);

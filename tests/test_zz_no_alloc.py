@@ -2,8 +2,8 @@
 vsr_retrieve (caller's workspace) through the C ABI. Both run the same
 kernels on the same inputs, so every output is compared bit for bit; the
 second call is smaller than the first (the static scratch still holds the
-first call's partial lists), the third takes the other scoring kernel
-(D not a multiple of 16). Sizes beyond the static scratch are refused."""
+first call's partial lists), the third has rows with a partial last piece (D
+not a multiple of 16). Sizes beyond the static scratch are refused."""
 import dataclasses
 import sys
 
@@ -61,7 +61,7 @@ def test_static_scratch_matches_workspace_entry_point():
         pytest.skip("no GPU")
     big = _case(W.VIDEO_22S_BANK, 0)          # 220 frames, 100k documents x 768
     small = _case(W.VIDEO_SMALL, 1)           # 40 frames, 300 documents x 64
-    odd = _case(W.VIDEO_SMALL, 2, dim=50)     # the per-document kernel
+    odd = _case(W.VIDEO_SMALL, 2, dim=50)     # a partial last piece
     assert big[0] > small[0] > 0 and odd[0] > 0
 
 
