@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 from paper_2601_01513_amd import workload as W
+from test_gpu_drafting import check_draft, run_draft, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -63,14 +64,37 @@ def test_f32_passes(cfg):
     one = v.verify(vis, ids, cids, wl.cand_len)
     v.prefill(vis, ids)
     two = v.score(cids, wl.cand_len)
-    # The first greedy token of a branch is the argmax of its last row; its
-    # log-prob, scored as one more token, is the largest of that row.
-    tok = v.draft(cids, wl.cand_len, 2)
-    torch.cuda.synchronize()
+    tok = run_draft(v, wl.cand_ids, wl.cand_len, 2)
     for out in (one, two):
         assert np.abs(out[0].cpu().numpy() - ref).max() <= 1e-4
         assert int(out[2].cpu()[0]) == am
-    assert tok.min() >= 0 and tok.max() < cfg.vocab
+    # Every greedy token is the oracle's, or within 2e-4 of its largest logit.
+    check_draft(cfg, tok, run_oracle(wl, wl.cand_ids, wl.cand_len, tok))
+
+
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[4]], ids=lambda c: c.name)
+def test_f32_greedy_token_in_the_last_partial_chunk(cfg):
+    """The head's rows of the greedy token and of the last vocabulary entry
+    trade places: the token is the last entry then, from a partial 64-entry
+    chunk. With both rows equal it is the lower of the two."""
+    torch = _torch()
+    from paper_2601_01513_amd.binding import Verifier
+    assert cfg.vocab % 64
+    wl, vis, ids, _ = _inputs(cfg, 1)
+    last = cfg.vocab - 1
+
+    def first_token():
+        v = Verifier(cfg, wl.weights, device="cuda", max_new=1)
+        v.prefill(vis, ids)
+        return int(run_draft(v, wl.cand_ids, wl.cand_len, 1)[0, 0])
+
+    t = first_token()
+    assert t != last
+    head = wl.weights["lm_head"]
+    head[[t, last]] = head[[last, t]].clone()
+    assert first_token() == last
+    head[t] = head[last]
+    assert first_token() == t
 
 
 def test_f32_candidates_do_not_see_each_others_nan():
