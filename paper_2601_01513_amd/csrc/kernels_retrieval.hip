@@ -336,12 +336,17 @@ __global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
     __syncthreads();
     const float *qp = q + (lane & 15) * QS + sub;
     for (int b = 0; b < nb; ++b) {
-      f32x4 acc[KG][NG];
+      // A sum for each of the four products of a piece, added up at the end. Error
+      // of the similarities (2-norm) over 500 / 768 / 1000 dimensions: 1.1e-7 / 1.2e-7 /
+      // 1.3e-7; as one chain over all of D 3.2e-7 / 4.6e-7 / 4.7e-7.
+      f32x4 acc[4][KG][NG];
       float dd[NG];
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
 #pragma unroll
-        for (int h = 0; h < KG; ++h) acc[h][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < KG; ++h)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[j][h][g] = f32x4{0.f, 0.f, 0.f, 0.f};
         dd[g] = 0.f;
       }
       auto piece = [&](int c, const f32x4 (&v)[NG]) {
@@ -354,12 +359,13 @@ __global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
           dd[g] += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            acc[0][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e0[j], acc[0][g], 0, 0, 0);
+            acc[j][0][g] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e0[j], acc[j][0][g], 0, 0, 0);
           if (two)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              acc[KG - 1][g] =
-                  __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e1[j], acc[KG - 1][g], 0, 0, 0);
+              acc[j][KG - 1][g] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], e1[j], acc[j][KG - 1][g], 0, 0, 0);
         }
       };
       auto step = [&](int c, const f32x4 (&v)[4][NG]) {
@@ -408,13 +414,15 @@ __global__ __launch_bounds__(RM_T) void k_retrieve_scan(const float *frame_emb,
         const int r = RG * h + (lane & 15);
         if (r < ng) {
 #pragma unroll
-          for (int g = 0; g < NG; ++g)
+          for (int g = 0; g < NG; ++g) {
+            const f32x4 dot = (acc[0][h][g] + acc[1][h][g]) + (acc[2][h][g] + acc[3][h][g]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int j = 16 * (w + 8 * g) + 4 * (lane >> 4) + i;
               const float den = qn[r] * dn[j];
-              sims[r][j] = den > 0.f ? acc[h][g][i] / den : 0.f;
+              sims[r][j] = den > 0.f ? dot[i] / den : 0.f;
             }
+          }
         }
       }
       __syncthreads();
