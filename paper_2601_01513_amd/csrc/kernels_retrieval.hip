@@ -175,7 +175,7 @@ __global__ __launch_bounds__(1024) void k_keyframes(const int32_t *hist, int NF,
 
 constexpr int RG = 16;       // keyframes per column group of the bank scan
 constexpr int RT = 256;      // documents a block scores at a time
-constexpr int kMaxLists = 512;  // lists per keyframe: two blocks a CU
+constexpr int kMaxLists = 256;  // lists per keyframe: a block a CU
 
 // A ranked candidate as one unsigned 64-bit key: the similarity's
 // order-preserving bits above the complement of the document index, so a
@@ -264,11 +264,12 @@ __device__ __forceinline__ void block_topk(const float (*sims)[RT], int g0, int 
 // (keyframe rows in LDS are padded with zeros to whole 16s, and by 4 floats
 // more so that the 16 rows of an LDS read fall into distinct banks).
 //
-// HBM-bound: the bank is read once per 16 KG keyframes. With a block per 256
+// HBM-bound: the bank is read once per group of keyframes. With a block per 256
 // documents and group of 16 frames, the empty blocks of a grid sized for
 // every frame being a keyframe (391 x 14 blocks for 220 frames) held LDS that
-// the others waited for, and 391 equal shares do not divide evenly over 256
-// CUs: 84 us for 12 keyframes over 100k x 768 (3.7 TB/s), now 71 us (4.3 TB/s).
+// the others waited for, and 391 shares of 256 documents do not divide evenly
+// over 256 CUs: 84 us for 12 keyframes over 100k x 768 (3.7 TB/s), in 256 equal
+// shares 70 us (4.4 TB/s).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int RM_T = 512;
 template <int KG>
@@ -454,7 +455,7 @@ __device__ __forceinline__ T get_agent(const T *p) {
 // per keyframe). As two launches the merge and the selection took 9.8 + 7.1 us
 // for 12 keyframes over 100k documents, now 7.7 us.
 constexpr int MERGE_T = 1024;
-constexpr int MERGE_PER = 8;
+constexpr int MERGE_PER = 4;
 static_assert(kMaxLists * 16 <= MERGE_T * MERGE_PER, "k <= 16 candidates of every list");
 __global__ __launch_bounds__(MERGE_T) void k_retrieve_merge(const key_t64 *part,
                                                             const int32_t *n_keys, int nlists,
@@ -584,18 +585,17 @@ hipError_t launch_retrieve(const float *frame_emb, const int32_t *key_idx, const
   key_t64 *part = static_cast<key_t64 *>(ws);
   // Up to 32 keyframes per pass over the bank if there may be more than 16 and
   // their rows (with 32 lists of similarities) fit the 160 KB of LDS. A list per
-  // block of documents, as many as the CUs hold blocks at once (and lists as the
-  // workspace); what a small bank leaves of them takes further groups of
-  // keyframes. (One block per list took the groups of a small bank in turn: 200
-  // keyframes against 156 and 5000 documents of 768 288 and 315 us, now 38 and
-  // 69; a grid sized for every frame being a keyframe 55 and 81 us.)
+  // block of documents, as many as the CUs hold blocks at once (one each, by their
+  // registers: in two rounds of 391 blocks 12 of at most 16 keyframes against 100k
+  // documents took 92 us, now 73); what a small bank leaves of them takes further
+  // groups of keyframes. (One block per list took the groups of a small bank in
+  // turn: 200 keyframes against 156 and 5000 documents of 768 288 and 315 us, now
+  // 38 and 69; a grid sized for every frame being a keyframe 55 and 81 us.)
   const size_t qrow = ((size_t)(D + 15) / 16 * 16 + 4) * sizeof(float);
   const bool wide = NF > RG && 2 * RG * (qrow + RT * sizeof(float)) <= (size_t)150 << 10;
   const int rows = wide ? 2 * RG : RG;
-  const size_t lds = rows * (qrow + RT * sizeof(float)) + 2048;
-  const int per_cu = (int)std::min<size_t>(2, std::max<size_t>(1, (size_t)(160 << 10) / lds));
-  const int blocks = kMaxLists / 2 * per_cu, nlists = std::min((ND + RT - 1) / RT, blocks);
-  const dim3 grid(nlists, std::min((NF + RG - 1) / RG, blocks / nlists));
+  const int nlists = std::min((ND + RT - 1) / RT, kMaxLists);
+  const dim3 grid(nlists, std::min((NF + RG - 1) / RG, kMaxLists / nlists));
   if (wide)
     k_retrieve_scan<2><<<grid, RM_T, rows * qrow, s>>>(frame_emb, key_idx, n_keys, docs, ND, D, k,
                                                        nlists, part, n_sel);

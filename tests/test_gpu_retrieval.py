@@ -160,8 +160,8 @@ def test_retrieval_sizes(nd, dim, k, K):
 
 
 def test_retrieval_million_documents():
-    """A bank of many batches per scan block (512 lists of 2048 documents, 8
-    batches each), whole 16-wide pieces."""
+    """A bank of many batches per scan block (256 lists of 4096 documents,
+    16 batches each), whole 16-wide pieces."""
     rc = W.RetrievalConfig("bank 2^20 x 16", 30, 16, 16, 4, 1 << 20, 16, 3, 8, 0.6)
     _say(f"case: {rc.name}")
     check_retrieval(rc, *W.make_retrieval(rc, 4))

@@ -56,9 +56,8 @@ def _scan_plan(nf, nk, nd, dim):
     row = ((dim + 15) // 16 * 16 + 4) * 4
     wide = nf > 16 and 32 * (row + 1024) <= 150 << 10
     rows = 32 if wide else 16
-    blocks = 256 * min(2, max(1, (160 << 10) // (rows * (row + 1024) + 2048)))
-    nlists = min((nd + 255) // 256, blocks)
-    ny = min((nf + 15) // 16, blocks // nlists)
+    nlists = min((nd + 255) // 256, 256)
+    ny = min((nf + 15) // 16, 256 // nlists)
     if nk <= 16 * ny:
         rows = 16
     groups = (nk + rows - 1) // rows
@@ -71,18 +70,18 @@ def _scan_plan(nf, nk, nd, dim):
     (40, 16, 300, 35, 3, 5, (16, 1, 1)),       # unaligned rows, a partial piece
     (40, 17, 300, 36, 16, 64, (16, 1, 1)),     # two groups side by side
     (70, 70, 2000, 100, 5, 40, (16, 1, 1)),    # five
-    (40, 40, 700, 900, 3, 9, (16, 1, 1)),      # one block per CU
+    (40, 40, 700, 900, 3, 9, (16, 1, 1)),      # long rows
     (40, 40, 66000, 900, 3, 9, (32, 2, 2)),    # ... and more documents than one batch each
-    (20, 20, 70001, 20, 4, 8, (32, 1, 1)),     # the second 16 of a group of 32
-    (70, 70, 70001, 20, 4, 8, (32, 3, 1)),     # three groups of 32 in turn
+    (20, 20, 65001, 20, 4, 8, (32, 1, 1)),     # the second 16 of a group of 32
+    (70, 70, 65001, 20, 4, 8, (32, 3, 1)),     # three groups of 32 in turn
     (300, 200, 90, 13, 16, 64, (16, 1, 1)),    # more than 1024 entries to select from
-    (300, 300, 20000, 13, 2, 9, (32, 2, 1)),   # groups of 32 side by side and in turn
-    (40, 40, 43600, 944, 3, 9, (16, 2, 1)),    # rows too long for 32: groups of 16 in turn
+    (300, 300, 20000, 13, 2, 9, (32, 4, 1)),   # groups of 32 side by side and in turn
+    (40, 40, 22000, 944, 3, 9, (16, 2, 1)),    # rows too long for 32: groups of 16 in turn
     (3, 1, 1, 1, 1, 1, (16, 1, 1)),
     # Several batches, the wave's second tile in use in every other one (128 and
     # 129 documents), its stored list merged, in a second group as well.
-    (40, 40, 512 * 257, 20, 4, 8, (32, 2, 2)),
-    (16, 16, 512 * 257, 20, 4, 8, (16, 1, 2)),
+    (40, 40, 256 * 257, 20, 4, 8, (32, 2, 2)),
+    (16, 16, 256 * 257, 20, 4, 8, (16, 1, 2)),
 ])
 def test_retrieve_groups(nf, nk, nd, dim, k, K, plan):
     assert _scan_plan(nf, nk, nd, dim) == plan
