@@ -529,6 +529,8 @@ __global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
   }
   const float scale_log2 = 1.4426950408889634f * rsqrtf((float)HD);
   L.thr = 8.f / scale_log2;
+  const int tok_first = a.t0 + q0 / G;
+  const int tok_last = a.t0 + min(q0 + QT - 1, TG - 1) / G;
   const int chunk = blockIdx.z;
   const long koff = (long)kvh * a.kv_npos * HD, boff = (long)kvh * a.bk_npos * HD;
   // With split keys the chunks follow the rows' first and last token. Eight
@@ -544,7 +546,6 @@ __global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
     const int r = q0 + h * (QT / HALVES);
     return a.t0 + min((r < TG ? r : q0) + QT / HALVES - 1, TG - 1) / G;
   };
-  const int tok_first = a.t0 + q0 / G;
   if (MODE == 0) {
     // Causal keys 0 .. the last token; with nchunks > 1 (few blocks on the chip)
     // chunk `chunk` takes an even share of the key tiles.
@@ -599,7 +600,7 @@ __global__ __launch_bounds__((Shape<PREC, NW>::NT)) void k_attn(AttnArgs a) {
     // branch tiles].
     const int pre_t = (a.P + KT - 1) / KT;
     const int lo = a.row_lo[tok_first] & ~(KT - 1);
-    const int hi = a.q_pos[last_tok(0)];
+    const int hi = a.q_pos[tok_last];
     const int tot = pre_t + (hi - lo) / KT + 1;
     const int c0 = (int)((long)tot * chunk / a.nchunks);
     const int c1 = (int)((long)tot * (chunk + 1) / a.nchunks);
