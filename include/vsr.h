@@ -133,7 +133,10 @@ typedef struct vsr_weights {
 typedef struct vsr_ctx vsr_ctx;
 
 /* Bytes of device workspace a context with this config needs (0 if the
- * config is invalid). Pure host computation. */
+ * config is invalid). Pure host computation. It holds the rows of a prefix and
+ * of max_cands candidates at once (vsr_verify is one pass for every dtype) and
+ * the LM head's partials: 8 bytes per scored row and 256 vocabulary entries
+ * (VSR_F32: 64). */
 size_t vsr_workspace_size(const vsr_config *cfg);
 
 /* Creates a context. `workspace` is a device buffer of at least
