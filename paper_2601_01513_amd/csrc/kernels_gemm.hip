@@ -1156,16 +1156,18 @@ __global__ __launch_bounds__(TL::NW * 64) void k_gemm_qkv_s(const f16 *__restric
 }
 
 // Tail tiles: the partials summed in split order, then the rotary and the
-// staged stores as above. Block (tail tile, 64-row quarter), 16 waves: wave w
-// sums head h = w % 2 of the pair for the 4-row groups g = w / 2 and w / 2 + 8,
-// then stores its eighth of that head's staging block. Bound by the round
+// staged stores as above. Block (tail tile, 64-row quarter), NW waves: wave w
+// sums head h = w % 2 of the pair for the 4-row groups g = w / 2, w / 2 + NW / 2,
+// .., then stores its share of that head's staging block. Bound by the round
 // trips of the partial loads: with 4 waves of 8 groups each the few blocks of
-// a short launch (144 at 512 rows of the 7B shape) took 29 us for 66 MB, now
-// 22 us (3 TB/s).
-template <int NS>
-__global__ __launch_bounds__(1024) void k_reduce_qkv(const float *__restrict__ part, Launch ln,
-                                                     int rows, int n_heads, int n_kv,
-                                                     QKVOut<f16> o) {
+// a short launch (144 at 512 rows of the 7B shape) took 29 us for 66 MB, with 16
+// 22 us (3 TB/s). Precise layers store their values one by one, unstaged; there 4
+// waves are the better form from 160 blocks on: 16 / 4 waves, QKV with its reduce,
+// 1.5B at 1280 / 2048 rows (160 / 256 blocks) 73/69, 77/71 us, 7B at 512 (144) 88/89.
+template <int NS, int NW>
+__device__ __forceinline__ void reduce_qkv(const float *__restrict__ part, const Launch &ln,
+                                           int rows, int n_heads, int n_kv,
+                                           const QKVOut<f16> &o) {
   __shared__ u32x4 lds[2 * 1024];  // a 16 KB staging block per head
   const int i = blockIdx.x >> 2, quarter = blockIdx.x & 3;
   int tm, tn;
@@ -1179,25 +1181,26 @@ __global__ __launch_bounds__(1024) void k_reduce_qkv(const float *__restrict__ p
   VtBlock vb;
   const bool staged = live && !precise &&
                       (value ? vt_block(o, n_heads, n_kv, slot, r0, rows, vb) : qk_staged_ok(o));
-  // The rotary entries of the thread's 8 rows, loaded beside the partials (in
+  // The rotary entries of the thread's rows, loaded beside the partials (in
   // the loop below they waited out two memory round trips per row group: the
   // position, then the entry).
-  float2 cs[2][4];
+  constexpr int NG = 32 / NW;  // 4-row groups per thread
+  float2 cs[NG][4];
   if (live && !value) {
-    int pos[2][4];
+    int pos[NG][4];
 #pragma unroll
-    for (int it = 0; it < 2; ++it)
+    for (int it = 0; it < NG; ++it)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        pos[it][j] = qkv_row_pos(o, min(r0 + 4 * (8 * it + (w >> 1)) + j, rows - 1));
+        pos[it][j] = qkv_row_pos(o, min(r0 + 4 * (NW / 2 * it + (w >> 1)) + j, rows - 1));
 #pragma unroll
-    for (int it = 0; it < 2; ++it)
+    for (int it = 0; it < NG; ++it)
 #pragma unroll
       for (int j = 0; j < 4; ++j) cs[it][j] = o.rope[(long)pos[it][j] * 64 + d];
   }
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int g = 8 * it + (w >> 1);
+  for (int it = 0; it < NG; ++it) {
+    const int g = NW / 2 * it + (w >> 1);
     float x1[4], x2[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1236,9 +1239,22 @@ __global__ __launch_bounds__(1024) void k_reduce_qkv(const float *__restrict__ p
   __syncthreads();
   if (!staged) return;
   if (value)
-    vt_copy_out<2>(stg, vb.vt, vb.npos, vb.crow0, 2 * (w >> 1));
+    vt_copy_out<NG>(stg, vb.vt, vb.npos, vb.crow0, NG * (w >> 1));
   else
-    qk_copy_out<2>(stg, o, n_heads, slot, r0, rows, 2 * (w >> 1));
+    qk_copy_out<NG>(stg, o, n_heads, slot, r0, rows, NG * (w >> 1));
+}
+
+template <int NS>
+__global__ __launch_bounds__(1024) void k_reduce_qkv(const float *__restrict__ part, Launch ln,
+                                                     int rows, int n_heads, int n_kv,
+                                                     QKVOut<f16> o) {
+  reduce_qkv<NS, 16>(part, ln, rows, n_heads, n_kv, o);
+}
+template <int NS>
+__global__ __launch_bounds__(256) void k_reduce_qkv_4(const float *__restrict__ part, Launch ln,
+                                                      int rows, int n_heads, int n_kv,
+                                                      QKVOut<f16> o) {
+  reduce_qkv<NS, 4>(part, ln, rows, n_heads, n_kv, o);
 }
 
 // ------------------------------------------------------ LM head + chunk LSE
@@ -1625,9 +1641,15 @@ hipError_t gemm_qkv_rope(const f16 *A, const void *W, bool w_f16, int rows, int 
   const Launch ln = plan_launch((rows + TL::BM - 1) / TL::BM, (nslots + 1) / 2, 8,
                                 K / BK * asplit);
   VSR_WLAUNCH(k_gemm_qkv, ln.blocks(), A, W16, rows, K, asplit, n_heads, n_kv, ln, out, part);
-  if (ln.ntail > 0)
-    VSR_REDUCE_LAUNCH(ln.nsplit, k_reduce_qkv, ln.ntail * 4, 1024, part, ln, rows, n_heads, n_kv,
-                      out);
+  if (ln.ntail > 0) {
+    const bool precise = out.q_lo || out.k_lo || out.vt_lo;
+    if (precise && ln.ntail * 4 >= 160)
+      VSR_REDUCE_LAUNCH(ln.nsplit, k_reduce_qkv_4, ln.ntail * 4, 256, part, ln, rows, n_heads,
+                        n_kv, out);
+    else
+      VSR_REDUCE_LAUNCH(ln.nsplit, k_reduce_qkv, ln.ntail * 4, 1024, part, ln, rows, n_heads,
+                        n_kv, out);
+  }
   return hipGetLastError();
 }
 
