@@ -233,9 +233,12 @@ __device__ __forceinline__ int qkv_cache_row(const QKVOut<f16> &o, int row) {
 }
 
 // qkv_store without the rotary: x1, x2 are the pair as stored (queries and
-// keys already rotated), crow the row's cache position.
+// keys already rotated), cache_pos() the row's cache position (asked for where a
+// key or value is stored: computed ahead of the branch it cost the tiles' QKV
+// epilogue 1.5 us a launch).
+template <class Pos>
 __device__ __forceinline__ void qkv_store_at(const QKVOut<f16> &o, int n_heads, int n_kv, int slot,
-                                             int row, int d, float x1, float x2, int crow) {
+                                             int row, int d, float x1, float x2, Pos cache_pos) {
   const bool second = row >= o.split;  // a candidate row of a fused pass
   const f16 h1 = static_cast<f16>(x1), h2 = static_cast<f16>(x2);
   const f16 l1 = static_cast<f16>(x1 - static_cast<float>(h1));
@@ -249,6 +252,7 @@ __device__ __forceinline__ void qkv_store_at(const QKVOut<f16> &o, int n_heads, 
       o.q_lo[off + d + 64] = l2;
     }
   } else {
+    const int crow = cache_pos();
     const int npos = second ? o.kv_npos2 : o.kv_npos;
     if (slot < n_heads + n_kv) {
       f16 *k = second ? o.k2 : o.k, *k_lo = second ? o.k2_lo : o.k_lo;
@@ -278,8 +282,7 @@ __device__ __forceinline__ void qkv_store_at(const QKVOut<f16> &o, int n_heads, 
 
 __device__ __forceinline__ void qkv_store_rotated(const QKVOut<f16> &o, int n_heads, int n_kv,
                                                   int slot, int row, int d, float x1, float x2) {
-  qkv_store_at(o, n_heads, n_kv, slot, row, d, x1, x2,
-               slot < n_heads ? 0 : qkv_cache_row(o, row));
+  qkv_store_at(o, n_heads, n_kv, slot, row, d, x1, x2, [&] { return qkv_cache_row(o, row); });
 }
 
 // The rotate-half pair of query / key slots turned by the rotary-table entry

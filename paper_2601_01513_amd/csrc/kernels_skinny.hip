@@ -494,7 +494,8 @@ __global__ __launch_bounds__(1024, WPE) void k_few(FewArgs a) {
         } else {
           const int slot = g >> 4;
           qk_turn(a.o, a.n_heads, a.n_kv, slot, v, v2, cs);
-          qkv_store_at(a.o, a.n_heads, a.n_kv, slot, r, (g & 15) * 4 + c, v, v2, crow);
+          qkv_store_at(a.o, a.n_heads, a.n_kv, slot, r, (g & 15) * 4 + c, v, v2,
+                       [&] { return crow; });
         }
       }
       if (EPI == FEW_QKV && g + (int)gridDim.x < ngroups) load_cs(g + gridDim.x);
