@@ -763,29 +763,9 @@ int prefill_chunks(int T, int n_heads, int n_kv) {
   return std::max(1, std::min(4, (384 + blocks - 1) / blocks));
 }
 
-hipError_t attn_prefill(const AttnArgs &a, bool precise, hipStream_t s) {
-  if (a.T <= a.t0) return hipSuccess;
-  if (a.nchunks < 1 || a.nchunks > 64 || (a.nchunks > 1 && a.t0 != 0))
-    return hipErrorInvalidValue;
-  if (precise && (!a.q_lo || !a.k_lo || !a.vt_lo)) return hipErrorInvalidValue;
-  return precise ? launch_precise<0>(a, s) : launch_attn<0, false>(a, s);
-}
-
-hipError_t attn_cascade(const AttnArgs &a, bool precise, hipStream_t s) {
-  if (a.T == 0 || a.t0 != 0) return a.T == 0 ? hipSuccess : hipErrorInvalidValue;
-  if (precise && (!a.q_lo || !a.k_lo || !a.vt_lo || !a.bk_lo || !a.bvt_lo))
-    return hipErrorInvalidValue;
-  if (a.q_pos) {  // draft pass
-    if (a.bk_valid <= 0) return hipErrorInvalidValue;
-    if (precise) return launch_precise<2>(a, s);
-    // Decode steps: all stacked query rows of a KV head in one wave.
-    if ((a.T - a.t0) * (a.n_heads / a.n_kv) <= Shape<false, 1>::QT)
-      return launch_attn<2, false, 1>(a, s);
-    return launch_attn<2, false>(a, s);
-  }
-  return precise ? launch_precise<1>(a, s) : launch_attn<1, false>(a, s);
-}
-
+// Kernels are laid out in the order of their first use here: the two of a
+// decode step stand together (3B drafting 148.1 -> 147.7 ms; the kernels are
+// the same instruction by instruction, two runs of one side differ by 0.4).
 hipError_t attn_merge(const AttnArgs &a, hipStream_t s) {
   if (a.T == 0 || a.nchunks == 1) return hipSuccess;
   if (a.nchunks > 64) return hipErrorInvalidValue;
@@ -795,6 +775,28 @@ hipError_t attn_merge(const AttnArgs &a, hipStream_t s) {
   else
     k_attn_merge<1><<<dim3(a.T, a.n_heads), 64, 0, s>>>(a);
   return hipGetLastError();
+}
+
+hipError_t attn_cascade(const AttnArgs &a, bool precise, hipStream_t s) {
+  if (a.T == 0 || a.t0 != 0) return a.T == 0 ? hipSuccess : hipErrorInvalidValue;
+  if (precise && (!a.q_lo || !a.k_lo || !a.vt_lo || !a.bk_lo || !a.bvt_lo))
+    return hipErrorInvalidValue;
+  if (a.q_pos) {  // draft pass
+    if (a.bk_valid <= 0) return hipErrorInvalidValue;
+    // Decode steps: all stacked query rows of a KV head in one wave.
+    if (!precise && (a.T - a.t0) * (a.n_heads / a.n_kv) <= Shape<false, 1>::QT)
+      return launch_attn<2, false, 1>(a, s);
+    return precise ? launch_precise<2>(a, s) : launch_attn<2, false>(a, s);
+  }
+  return precise ? launch_precise<1>(a, s) : launch_attn<1, false>(a, s);
+}
+
+hipError_t attn_prefill(const AttnArgs &a, bool precise, hipStream_t s) {
+  if (a.T <= a.t0) return hipSuccess;
+  if (a.nchunks < 1 || a.nchunks > 64 || (a.nchunks > 1 && a.t0 != 0))
+    return hipErrorInvalidValue;
+  if (precise && (!a.q_lo || !a.k_lo || !a.vt_lo)) return hipErrorInvalidValue;
+  return precise ? launch_precise<0>(a, s) : launch_attn<0, false>(a, s);
 }
 
 }  // namespace vsr
